@@ -297,13 +297,14 @@ int64_t ctu_static_scratch_bytes(void);
  *                             row by row (3D boxes with n[0] <= 37; others
  *                             keep the rectangles);
  *              CTU_TC_AUTO    per box, the one that needs fewer blocks
- *  tc_chunk  : planes per t^n block along the marching axis, 1..4096; 0 = 16
- *  x_pencils : x-sweep pencils per block, 1..64; 0 = the count that idles
- *              the fewest lanes
+ *  tc_chunk  : planes per t^n block along the marching axis, 1..4096; 0 = 1, 2
+ *              or 4 by the number of blocks
+ *  x_pencils : x-sweep pencils per block, 1..64; 0 = the count, or the runs
+ *              of one pencil, that the plan's boxes fill the chip with best
  *  xcd_order : 1 = launch order that gives each XCD a contiguous run of
  *              tiles (halo lines shared in one L2); 0 = place order
  *  yz_segments: blocks per y- and z-sweep column of 64 pencils, 1..8
- *              (0 = 1): each block updates a run of the line's cells and
+ *              (0 = as many as fill the chip): each block updates a run of the line's cells and
  *              first recomputes the two predicted states below its run, so
  *              results do not depend on it; more, shorter blocks leave fewer
  *              compute units with a single block at the end of a launch */

@@ -338,9 +338,10 @@ template <int DIM> struct PTile {
     static constexpr int TX = (DIM == 3) ? 32 : NT;
     static constexpr int TY = (DIM == 3) ? 8 : 1;
     static constexpr int HX = TX + 2, HY = (DIM == 3) ? TY + 2 : 1, HP = HX * HY;
-    // planes per block along the marching axis (measured at 256^3: k_pflux
-    // 0.76 / 0.82 / 0.88 ms with 4 / 8 / 16, k_pdiv 0.77 / 0.73 / 0.73)
-    static constexpr int LM_FLUX = 4, LM_DIV = 8;
+    // planes per block along the marching axis come with the launch: at most
+    // 4 for k_pflux and 8 for k_pdiv (measured at 256^3: k_pflux 0.76 / 0.82 /
+    // 0.88 ms with 4 / 8 / 16, k_pdiv 0.77 / 0.73 / 0.73), fewer on boxes
+    // whose blocks would leave compute units idle
 };
 
 template <typename R> struct PArgs {
@@ -349,6 +350,7 @@ template <typename R> struct PArgs {
     const R *V;          // primitive state (workspace)
     R *PF;               // face slots (workspace): NPF * DIM planes per cell
     KOpts o;
+    int lm;              // planes per block along the marching axis
 };
 
 // the energy slot plus the conduction flux of normal component Fn and
@@ -510,7 +512,7 @@ __global__ __launch_bounds__(NT) void k_pflux(PArgs<R> a)
     const bool fx = x <= hi[0] && iny;
     const bool fy = DIM == 3 && inx && y <= hi[1];
     const bool fm = inx && iny;
-    const int m0 = lo[AM] + 1 + tl.c, m1 = min(m0 + PT::LM_FLUX - 1, hi[AM]);
+    const int m0 = lo[AM] + 1 + tl.c, m1 = min(m0 + a.lm - 1, hi[AM]);
 
     int r0 = 0, r1 = 1, r2 = 2;  // ring slots of planes m-1, m, m+1
     pf_stage<DIM>(&S[r0][0], Vb, bx, lo, hi, x0, y0, m0 - 1);
@@ -594,7 +596,7 @@ __global__ __launch_bounds__(NT) void k_pdiv(PArgs<R> a)
     const bool fy = DIM == 3 && x <= hi[0] - 1 && y <= hi[1];
     const bool fm = x <= hi[0] - 1 && iny;
     const bool own = fm && tx < PT::TX - 1 && (DIM == 2 || ty < PT::TY - 1);
-    const int m0 = lo[AM] + 1 + tl.c, m1 = min(m0 + PT::LM_DIV - 1, hi[AM] - 1);
+    const int m0 = lo[AM] + 1 + tl.c, m1 = min(m0 + a.lm - 1, hi[AM] - 1);
     const int sM = (DIM == 3) ? bx.N[0] * bx.N[1] : bx.N[0];
     const R ix = R(1.0 / bx.dx[0]), iy = R(1.0 / bx.dx[1]), iz = R(1.0 / bx.dx[2]);
 
@@ -762,7 +764,6 @@ template <typename R> __device__ __forceinline__ R diff_coeff(const KOpts &o, R 
 template <int DIM> struct TTile {
     static constexpr int TX = (DIM == 3) ? 32 : NT;
     static constexpr int TY = (DIM == 3) ? 8 : 1;
-    static constexpr int LM = 16;   // default planes per block along the marching axis
     // strip tiles (3D): the last SW <= 2 positions of each row of the region
     // when its width leaves that many beyond the TX-wide rectangles, SH rows
     // per block (positions on the first two waves, the strip's extra faces
@@ -1376,15 +1377,20 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
     const int npos_tot = nT0 * nT1;
     const int pos0 = tl.a;
     int items;
-    int P = 0;
     // y / z: the tile owns rows [r0, r1) of its 64 pencils (faces and updates
     // below those rows); a segment that starts inside the line first re-runs
     // rows r0 - 2 and r0 - 1 for the states and the flux below row r0, with
-    // the same arithmetic as the segment that owns them
+    // the same arithmetic as the segment that owns them.  x: b whole pencils
+    // end to end, or (b < 0) -b rows of one pencil from row c
     int r0 = 0, rs = 0;
     if (D == 0) {
-        P = min(tl.b, npos_tot - pos0);
-        items = P * Lc;
+        if (tl.b > 0) {
+            items = min(tl.b, npos_tot - pos0) * Lc;
+        } else {
+            r0 = tl.c;
+            rs = max(r0 - 2, 0);
+            items = r0 - tl.b - rs;
+        }
     } else {
         r0 = tl.b;
         rs = max(r0 - 2, 0);
@@ -1413,13 +1419,33 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
     for (int e = 0; e < 3; e++)
         if (e < dim) rdx2 += 2.0 / (bx.dx[e] * bx.dx[e]);
 
+    // the item's row s and pencil pos: x, stepped by NT items a round
+    int s = 0, pos = 0;
+    const int sstep = NT % Lc, pstep = NT / Lc;
+    if (D == 0) {
+        s = rs + tid % Lc;
+        pos = pos0 + tid / Lc;
+        if (tl.b < 0) {
+            s = rs + tid;
+            pos = pos0;
+        }
+    }
     for (int base = 0; base < items; base += NT) {
         const int kit = base + tid;
         bool valid = kit < items;
-        int s = 0, pos = 0;
         if (D == 0) {
-            s = kit % Lc;
-            pos = pos0 + kit / Lc;
+            if (base > 0) {
+                if (tl.b > 0) {
+                    s += sstep;
+                    pos += pstep;
+                    if (s >= Lc) {
+                        s -= Lc;
+                        pos++;
+                    }
+                } else {
+                    s += NT;
+                }
+            }
         } else {
             s = rs + kit / DEL;
             pos = pos0 + kit % DEL;

@@ -133,6 +133,17 @@ struct ctu_plan {
     int nrefl_cells = 0;
     // launch shape of the t^n and sweep tables (see ctu_shape)
     ctu_shape shape{ CTU_TC_AUTO, 0, 0, 1, 0 };
+    // the work split in use: the shape's values, those left at 0 chosen by
+    // auto_split for the plan's boxes
+    static constexpr int kWhole = 1 << 30;
+    struct Split {
+        int lm = 4;                 // t^n planes per block
+        int xp = 1;                 // x-sweep pencils per block, where a line is not split into
+        int xrows = kWhole;         // runs of about this many updated rows, one run per block
+        int rows[3] = { kWhole, kWhole, kWhole };  // y / z sweep: the same, 64 pencils per block
+        int segs = 0;               // > 0: y / z lines in this many segments instead
+        int lm_div = 8, lm_flux = 4;  // k_pdiv / k_pflux planes per block
+    } split, split_auto;
     std::string tune_key;  // autotune cache key of the option set and box extents
     // graph
     hipGraph_t graph = nullptr;
@@ -165,27 +176,6 @@ void free_plan(ctu_plan *p)
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     delete p;
-}
-
-// pencils per block along x: the P that keeps P*(n+2) closest to a multiple
-// of the block size (fewest idle lanes in the last round)
-int pencils_per_block(int L, int npos)
-{
-    int best = 1;
-    double best_eff = 0.0;
-    for (int P = 1; P <= 64; P++) {
-        if (P > npos && P > 1) break;
-        long long items = (long long)P * L;
-        long long rounds = (items + NT - 1) / NT;
-        double eff = (double)items / (double)(rounds * NT);
-        if (eff > best_eff + 1e-9 || (eff > best_eff - 1e-9 && P * L <= 16 * NT)) {
-            if (eff >= best_eff - 1e-9) {
-                best_eff = std::max(best_eff, eff);
-                best = P;
-            }
-        }
-    }
-    return best;
 }
 
 // Launch order that gives each XCD a contiguous run of the tile list.  The
@@ -246,11 +236,165 @@ bool use_flat(const ctu_plan *p, const KBox &bx)
     return flat < rect_tiles_per_plane(bx);
 }
 
-int tc_chunk(const ctu_plan *p) { return p->shape.tc_chunk > 0 ? p->shape.tc_chunk : TTile<3>::LM; }
+// Work split of the sweeps.  A block runs in rounds of 256 items; longer
+// blocks repeat less work at their ends, shorter ones put more blocks on the
+// chip and leave a shorter tail.  SplitCost estimates a launch's time, in
+// units of one round's cost on a compute unit that holds `res` blocks (the
+// register-bound residence): whole batches of 256 * res blocks cost res
+// units per round; the blocks left over run fewer to a compute unit, where a
+// round takes kConc units (one block alone is bound by the latency of its
+// ~1500 dependent instructions) plus kPro rounds to start.  Against measured
+// sweeps (64^3 .. 256^3, 131 x 97 x 75, FP32 and FP64, 1 .. 8 runs per line)
+// the estimate is within 12 %: 256^3 FP32 715 / 664 / 657 / 662 / 690 us with
+// 1 / 2 / 3 / 4 / 8 runs, 192^3 FP64 880 / 726 / 686 / 683 / 719.
+constexpr int kCus = 256;
+
+struct SplitCost {
+    double work = 0.0, longest = 0.0;  // rounds over all blocks, of the longest block
+    long long blocks = 0;
+    // n blocks over `items` items each
+    void add(long long n, long long items)
+    {
+        const double rounds = (double)((items + NT - 1) / NT);
+        blocks += n;
+        // waves without items skip their work but not the round's latency
+        work += (double)n * 0.5 * (rounds + (double)((items + 63) / 64) / 4.0);
+        longest = std::max(longest, rounds);
+    }
+    double time(int res) const
+    {
+        constexpr double kConc[4] = { 0.0, 1.6, 2.4, 3.0 }, kPro = 0.6;
+        const long long slots = (long long)kCus * res, full = blocks / slots, rem = blocks % slots;
+        const double avg = work / (double)blocks;
+        double t = (double)full * avg * res;
+        if (rem > 0) {
+            const int conc = (int)((rem + kCus - 1) / kCus);
+            t += (longest + kPro) * (conc >= res ? (double)res : kConc[conc]);
+        }
+        return t;
+    }
+};
+
+// x-sweep blocks of P whole pencils
+SplitCost x_pencil_cost(const ctu_plan *p, int P)
+{
+    SplitCost c;
+    for (const KBox &bx : p->hboxes) {
+        const long long npos = (long long)bx.n[1] * bx.n[2], L = bx.n[0] + 2, q = std::min<long long>(P, npos);
+        c.add(npos / q, q * L);
+        if (npos % q) c.add(1, npos % q * L);
+    }
+    return c;
+}
+
+// The runs of a line of n cells (rows 0 .. n + 1; row s >= 2 updates the cell
+// below it) for a target of `rows` updated rows per block: equal numbers of
+// updated rows, every run with the two rows below them.
+int run_rows(int n, int rows)
+{
+    const int S = std::max(1, std::min((n + rows / 2) / rows, n));
+    return (n + S - 1) / S;
+}
+
+// sweep blocks of about `rows` rows of one pencil (x) or of 64 pencils (y, z);
+// every run after a line's first re-runs two rows below it
+SplitCost row_cost(const ctu_plan *p, int D, int rows)
+{
+    SplitCost c;
+    const int dim = p->opts.dim, T0 = (D == 0) ? 1 : 0, T1 = (D == 2) ? 1 : 2;
+    for (const KBox &bx : p->hboxes) {
+        const long long npos = (long long)bx.n[T0] * (T1 < dim ? bx.n[T1] : 1);
+        const long long lines = (D == 0) ? npos : (npos + 63) / 64, lanes = (D == 0) ? 1 : 64;
+        const int n = bx.n[D], run = run_rows(n, rows), S = (n + run - 1) / run;
+        if (S > 1) c.add(lines * (S - 1), (run + 2) * lanes);
+        c.add(lines, (n - (S - 1) * run + 2) * lanes);
+    }
+    return c;
+}
+
+// in-plane tiles of the t^n region and of the parabolic kernels (whose
+// overlapping k_pdiv tiles set the larger count)
+long long tc_tiles_per_plane(const ctu_plan *p, const KBox &bx)
+{
+    if (p->opts.dim == 2) return (bx.n[0] + 2 + TTile<2>::TX - 1) / TTile<2>::TX;
+    if (use_flat(p, bx)) return ((long long)(bx.n[0] + 3) * (bx.n[1] + 3) + NT - 1) / NT;
+    return rect_tiles_per_plane(bx);
+}
+
+// blocks of `lm` planes over every box
+template <typename F> long long plane_blocks(const ctu_plan *p, int lm, F per_plane)
+{
+    long long n = 0;
+    for (const KBox &bx : p->hboxes) n += per_plane(bx) * ((bx.n[p->opts.dim - 1] + 1 + lm) / lm);
+    return n;
+}
+
+// The split of the fields that a shape leaves at 0; near ties go to the
+// candidate listed first.
+ctu_plan::Split auto_split(const ctu_plan *p)
+{
+    ctu_plan::Split s;
+    const int dim = p->opts.dim;
+    const int res = (p->esize == 4) ? 3 : 2;  // blocks per compute unit that the registers allow
+    const long long slots = (long long)kCus * res;
+    auto pick = [&](auto cost, const std::vector<int> &cand) {
+        int best = 0;
+        double bt = 0.0;
+        for (int v : cand) {
+            const double t = cost(v).time(res);
+            if (best == 0 || t < 0.98 * bt) {
+                best = v;
+                bt = t;
+            }
+        }
+        return std::make_pair(best, bt);
+    };
+    // t^n kernel: four planes per block (256^3 FP32 933 us against 1004 / 1063
+    // with 8 / 16 planes, 192^3 FP64 882 / 903 / 959) while that is twelve
+    // batches of blocks or more, then two (131 x 97 x 75 FP64, 2.5 batches:
+    // 152 -> 135 us; 160^3 non-ideal, 10 batches: 381 -> 357), and one where
+    // two leave the chip's second batch half empty (64^3: 34 / 28 / 27 us with
+    // 4 / 2 / 1)
+    auto tct = [&](const KBox &bx) { return tc_tiles_per_plane(p, bx); };
+    s.lm = plane_blocks(p, 4, tct) >= 12 * slots ? 4 : (2 * plane_blocks(p, 2, tct) >= 3 * slots ? 2 : 1);
+    for (int D = 1; D < dim; D++) {
+        std::vector<int> cand;
+        for (int S : { 2, 3, 4, 1, 5, 6, 8 }) cand.push_back((p->hboxes[0].n[D] + S - 1) / S);
+        for (int r : { 62, 46, 30, 22, 18, 14, 10, 6, 2 }) cand.push_back(r);  // rows + 2 in whole rounds
+        s.rows[D] = pick([&](int v) { return row_cost(p, D, v); }, cand).first;
+    }
+    const auto xp = pick([&](int v) { return x_pencil_cost(p, v); }, { 16, 32, 8, 64, 4, 2, 1 });
+    const auto xr = pick([&](int v) { return row_cost(p, 0, v); }, { 1022, 510, 254, 190, 126, 62, 30 });
+    s.xp = xp.first;
+    if (xr.second < 0.95 * xp.second) s.xrows = xr.first;
+    if (p->opts.parabolic_mask) {
+        auto pt = [&](const KBox &bx) {
+            return (long long)((bx.n[0] + PTile<3>::TX) / PTile<3>::TX) * ((bx.n[1] + PTile<3>::TY) / PTile<3>::TY);
+        };
+        auto pt2 = [&](const KBox &bx) { return (long long)((bx.n[0] + PTile<2>::TX) / PTile<2>::TX); };
+        auto nb = [&](int lm) { return dim == 3 ? plane_blocks(p, lm, pt) : plane_blocks(p, lm, pt2); };
+        s.lm_div = nb(8) >= 2 * slots ? 8 : (nb(4) >= slots ? 4 : 2);
+        s.lm_flux = nb(4) >= 2 * slots ? 4 : (nb(2) >= slots ? 2 : 1);
+    }
+    return s;
+}
+
+// the shape's values, with the automatic ones where it holds 0
+void resolve_split(ctu_plan *p)
+{
+    p->split = p->split_auto;
+    const ctu_shape &sh = p->shape;
+    if (sh.tc_chunk > 0) p->split.lm = sh.tc_chunk;
+    if (sh.x_pencils > 0) {
+        p->split.xp = sh.x_pencils;
+        p->split.xrows = ctu_plan::kWhole;
+    }
+    if (sh.yz_segments > 0) p->split.segs = sh.yz_segments;
+}
 
 // Entries of the shape-dependent tables for the largest shape: one-plane
 // t^n chunks in the layout with more blocks per plane, one pencil per x-sweep
-// block, eight y / z segments.
+// block or the automatic runs of one, eight y / z segments or the automatic ones.
 void shape_capacity(const ctu_plan *p, size_t cap[4])
 {
     const int dim = p->opts.dim;
@@ -263,7 +407,9 @@ void shape_capacity(const ctu_plan *p, size_t cap[4])
         for (int D = 0; D < dim; D++) {
             int T0 = (D == 0) ? 1 : 0, T1 = (D == 2) ? 1 : 2;
             long long npos = (long long)bx.n[T0] * ((T1 < dim) ? bx.n[T1] : 1);
-            cap[1 + D] += (size_t)(D == 0 ? npos : ((npos + 63) / 64) * 8);
+            const int run = run_rows(bx.n[D], D == 0 ? p->split_auto.xrows : p->split_auto.rows[D]);
+            const long long runs = (bx.n[D] + run - 1) / run;
+            cap[1 + D] += (size_t)(D == 0 ? npos * runs : ((npos + 63) / 64) * std::max(8LL, runs));
         }
     }
 }
@@ -275,7 +421,9 @@ ctu_status build_shape_tables(ctu_plan *p)
     const int dim = p->opts.dim;
     p->t_tc.h.clear();
     for (int D = 0; D < 3; D++) p->t_sweep[D].h.clear();
-    const int LM = tc_chunk(p);
+    resolve_split(p);
+    const ctu_plan::Split &sp = p->split;
+    const int LM = sp.lm;
     for (int b = 0; b < (int)p->hboxes.size(); b++) {
         const KBox &bx = p->hboxes[b];
         // t^n marching kernel: in-plane tiles of the region [g-1, g+n]
@@ -300,18 +448,34 @@ ctu_status build_shape_tables(ctu_plan *p)
             int T0 = (D == 0) ? 1 : 0, T1 = (D == 2) ? 1 : 2;
             int npos = bx.n[T0] * ((T1 < dim) ? bx.n[T1] : 1);
             if (D == 0) {
-                int P = p->shape.x_pencils > 0 ? std::min(p->shape.x_pencils, npos)
-                                               : pencils_per_block(bx.n[0] + 2, npos);
-                for (int s = 0; s < npos; s += P) p->t_sweep[0].h.push_back(KTile{ b, s, P, 0 });
+                const int Lc = bx.n[0] + 2, run = run_rows(bx.n[0], sp.xrows);
+                if (run < bx.n[0]) {
+                    // runs of one pencil: c holds the first row, b < 0 the number of rows from there
+                    for (int s = 0; s < npos; s++)
+                        for (int k = 0; k < bx.n[0]; k += run) {
+                            const int r0 = k ? k + 2 : 0;
+                            p->t_sweep[0].h.push_back(KTile{ b, s, r0 - std::min(Lc, k + run + 2), r0 });
+                        }
+                } else {
+                    const int P = std::min(sp.xp, npos);
+                    for (int s = 0; s < npos; s += P) p->t_sweep[0].h.push_back(KTile{ b, s, P, 0 });
+                }
             } else {
                 // rows [r0, r1) of the line of Lc items per tile: more, shorter
-                // blocks, so that the last blocks of the launch keep more
-                // waves per SIMD (each later segment re-runs two rows)
+                // blocks, so that the launch fills the chip and its last blocks
+                // keep more waves per SIMD (each later segment re-runs two rows)
                 const int Lc = bx.n[D] + 2;
-                const int S = std::max(1, std::min(std::max(p->shape.yz_segments, 1), Lc / 2));
-                const int L = (Lc + S - 1) / S;
-                for (int s = 0; s < npos; s += 64)
-                    for (int r0 = 0; r0 < Lc; r0 += L) p->t_sweep[D].h.push_back(KTile{ b, s, r0, std::min(Lc, r0 + L) });
+                if (sp.segs > 0) {
+                    const int S = std::max(1, std::min(sp.segs, Lc / 2));
+                    const int L = (Lc + S - 1) / S;
+                    for (int s = 0; s < npos; s += 64)
+                        for (int r0 = 0; r0 < Lc; r0 += L) p->t_sweep[D].h.push_back(KTile{ b, s, r0, std::min(Lc, r0 + L) });
+                } else {
+                    const int run = run_rows(bx.n[D], sp.rows[D]);
+                    for (int s = 0; s < npos; s += 64)
+                        for (int k = 0; k < bx.n[D]; k += run)
+                            p->t_sweep[D].h.push_back(KTile{ b, s, k ? k + 2 : 0, std::min(Lc, k + run + 2) });
+                }
             }
         }
     }
@@ -366,11 +530,9 @@ void add_mt_tiles(TileSet &ts, int b, const KBox &bx, int D, int dim)
 // Parabolic flux tiles: TX x TY in-plane cells by LM planes.  k_pflux: the
 // n + 1 face cells g .. g+n per axis, tiles side by side; k_pdiv: the n + 2
 // region cells g-1 .. g+n, tiles overlapping by one column (and row).
-void add_pf_tiles(TileSet &ts, int b, const KBox &bx, int dim, bool div)
+void add_pf_tiles(TileSet &ts, int b, const KBox &bx, int dim, bool div, int LM)
 {
     const int TX = (dim == 3) ? PTile<3>::TX : PTile<2>::TX, TY = (dim == 3) ? PTile<3>::TY : PTile<2>::TY;
-    const int LM = div ? ((dim == 3) ? PTile<3>::LM_DIV : PTile<2>::LM_DIV)
-                       : ((dim == 3) ? PTile<3>::LM_FLUX : PTile<2>::LM_FLUX);
     const int k = div ? 2 : 1, sx = div ? TX - 1 : TX, sy = (div && dim == 3) ? TY - 1 : TY;
     const int ex = bx.n[0] + k, ey = (dim == 3) ? bx.n[1] + k : 1, em = bx.n[dim - 1] + k;
     for (int m0 = 0; m0 < em; m0 += LM)
@@ -382,6 +544,7 @@ ctu_status build_tables(ctu_plan *p)
 {
     const int dim = p->opts.dim;
     const bool mt = p->opts.corner == CTU_CORNER_MT;
+    p->split_auto = auto_split(p);
     for (int b = 0; b < (int)p->hboxes.size(); b++) {
         const KBox &bx = p->hboxes[b];
         add_linear_tiles(p->t_cells, b, bx.cells);
@@ -389,8 +552,8 @@ ctu_status build_tables(ctu_plan *p)
         if (mt)
             for (int D = 0; D < dim; D++) add_mt_tiles(p->t_mt[D], b, bx, D, dim);
         if (p->opts.parabolic_mask) {
-            add_pf_tiles(p->t_pf, b, bx, dim, false);
-            add_pf_tiles(p->t_pd, b, bx, dim, true);
+            add_pf_tiles(p->t_pf, b, bx, dim, false, p->split_auto.lm_flux);
+            add_pf_tiles(p->t_pd, b, bx, dim, true, p->split_auto.lm_div);
         }
     }
     xcd_order(p->t_pf.h);
@@ -478,6 +641,7 @@ template <typename R> hipError_t launch_pflux(ctu_plan *p, const R *V, int div, 
     pa.tiles = ts.d;
     pa.V = V;
     pa.PF = (R *)p->wsPF;
+    pa.lm = div ? p->split_auto.lm_div : p->split_auto.lm_flux;
     pa.o = p->ko;
     if constexpr (sizeof(R) == 4) return launch_pflux_f32(p->opts.dim, div, (int)ts.n(), pa, s);
     else return launch_pflux_f64(p->opts.dim, div, (int)ts.n(), pa, s);
@@ -552,7 +716,7 @@ ctu_status enqueue_step(ctu_plan *p, const void *U_in, void *U_out, const double
         ta.flag = p->wsFlag;
         ta.params = params;
         ta.o = p->ko;
-        ta.lm = tc_chunk(p);
+        ta.lm = p->split.lm;
         hipError_t e;
         if constexpr (sizeof(R) == 4)
             e = launch_tcouple_f32(dim, par ? 1 : 0, p->combo, p->t_tc.n(), ta, s);
@@ -630,7 +794,7 @@ ctu_status check_shape(const ctu_shape *sh)
     if (sh->tc_chunk < 0 || sh->tc_chunk > 4096) return fail(CTU_ERR_ARG, "tc_chunk must be 0 (default) or 1..4096");
     if (sh->x_pencils < 0 || sh->x_pencils > 64) return fail(CTU_ERR_ARG, "x_pencils must be 0 (auto) or 1..64");
     if (sh->xcd_order != 0 && sh->xcd_order != 1) return fail(CTU_ERR_ARG, "xcd_order must be 0 or 1");
-    if (sh->yz_segments < 0 || sh->yz_segments > 8) return fail(CTU_ERR_ARG, "yz_segments must be 0 (one) or 1..8");
+    if (sh->yz_segments < 0 || sh->yz_segments > 8) return fail(CTU_ERR_ARG, "yz_segments must be 0 (auto) or 1..8");
     return CTU_OK;
 }
 
