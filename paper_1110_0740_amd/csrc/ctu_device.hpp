@@ -41,13 +41,50 @@ template <int D> struct Ax {
 };
 
 template <typename R> __device__ __forceinline__ R sq(R x) { return x * x; }
-// 1/sqrt(x): the hardware reciprocal root in FP32 (the FP32 unit runs with
-// approximate divide / sqrt and flushed subnormals), the correctly rounded
-// quotient in FP64
-template <typename R> __device__ __forceinline__ R rsq(R x)
+// Reciprocal, quotient, square root and reciprocal square root.  FP32 takes
+// the hardware's approximations (the FP32 unit runs with approximate divide /
+// sqrt and flushed subnormals).  FP64 refines the hardware's seeds (relative
+// error about 2^-23) by Newton steps in fused arithmetic to the rounding of
+// the result, without the range scaling and final correct rounding of the
+// language's operators: 6 / 9 / 11 / 6 instructions instead of 11 / 11 / 17 /
+// 28, every one in the dependent chains of the Riemann solver and the
+// eigensystem, which run at two waves per SIMD (the FP64 t^n kernel spent 38 %
+// of its instructions in the operators).  div_fixup restores the results for
+// zero, infinite and NaN operands.
+__device__ __forceinline__ float rcp(float x) { return 1.0f / x; }
+__device__ __forceinline__ double rcp(double x)
 {
-    if constexpr (sizeof(R) == 4) return __builtin_amdgcn_rsqf(x);
-    else return R(1) / sqrt(x);
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return __builtin_amdgcn_div_fixup(y, x, 1.0);
+}
+__device__ __forceinline__ float quot(float a, float b) { return a / b; }
+__device__ __forceinline__ double quot(double a, double b)
+{
+    double y = __builtin_amdgcn_rcp(b);
+    y = fma(fma(-b, y, 1.0), y, y);
+    y = fma(fma(-b, y, 1.0), y, y);
+    const double q = a * y;
+    return __builtin_amdgcn_div_fixup(fma(fma(-b, q, a), y, q), b, a);
+}
+__device__ __forceinline__ float root(float x) { return sqrtf(x); }
+__device__ __forceinline__ double root(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    // +-0 and +infinity are their own roots (class bits 5, 6 and 9)
+    return __builtin_amdgcn_class(x, 0x260) ? x : g;
+}
+__device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
+__device__ __forceinline__ double rsq(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x), e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 template <typename R> __device__ __forceinline__ R sgn1(R a) { return a < R(0) ? R(-1) : R(1); }
 
@@ -74,7 +111,7 @@ template <typename R> __device__ __forceinline__ void p2c_mhd(const R *V, R *U, 
 template <typename R> __device__ __forceinline__ int c2p_mhd(const R *U, R *V, R gm1)
 {
     R rho = U[RHO];
-    R ir = R(1) / rho;
+    R ir = rcp(rho);
     V[RHO] = rho;
     V[MX1] = U[MX1] * ir;
     V[MX2] = U[MX2] * ir;
@@ -86,24 +123,27 @@ template <typename R> __device__ __forceinline__ int c2p_mhd(const R *U, R *V, R
     R kin = U[MX1] * V[MX1] + U[MX2] * V[MX2] + U[MX3] * V[MX3];
     R mag = sq(U[BX1]) + sq(U[BX2]) + sq(U[BX3]);
     V[PRS] = gm1 * (U[ENG] - R(0.5) * (kin + mag));
+    const R vs = V[MX1] + V[MX2] + V[MX3];
     int f = 0;
-    if (!(rho > R(0))) f |= F_RHO;
-    if (!(V[PRS] > R(0))) f |= F_PRS;
-    if (isnan(V[PRS]) || isnan(V[MX1] + V[MX2] + V[MX3])) f |= F_NAN;
+    if (!(rho > R(0) && V[PRS] > R(0) && vs == vs)) {  // rare: which of them
+        if (!(rho > R(0))) f |= F_RHO;
+        if (!(V[PRS] > R(0))) f |= F_PRS;
+        if (isnan(V[PRS]) || isnan(vs)) f |= F_NAN;
+    }
     return f;
 }
 
 // fast magnetosonic speed along D
 template <int D, typename R> __device__ __forceinline__ R cfast_mhd(const R *V, R gam)
 {
-    R ir = R(1) / V[RHO];
+    R ir = rcp(V[RHO]);
     R a2 = gam * V[PRS] * ir;
     R b2 = (sq(V[BX1]) + sq(V[BX2]) + sq(V[BX3])) * ir;
     R bn2 = sq(V[BX1 + D]) * ir;
     R s = a2 + b2;
     R disc = s * s - R(4) * a2 * bn2;
     disc = disc > R(0) ? disc : R(0);
-    return sqrt(R(0.5) * (s + sqrt(disc)));
+    return root(R(0.5) * (s + root(disc)));
 }
 
 // conserved state and hyperbolic flux along D (GLM rows left to the caller)
@@ -421,7 +461,7 @@ __device__ __forceinline__ void hll(const R *VL, const R *VR, R *F, R &smax, R g
     phys_flux<D, PHYS>(VL, UL, FL, gam, ch, glm);
     phys_flux<D, PHYS>(VR, UR, FR, gam, ch, glm);
     // upwind or fan flux, selected per lane
-    R id = R(1) / (SR - SL);
+    R id = rcp(SR - SL);
 #pragma unroll
     for (int q = 0; q < NV; q++) {
         R Fh = (SR * FL[q] - SL * FR[q] + SL * SR * (UR[q] - UL[q])) * id;
@@ -470,7 +510,7 @@ __device__ __forceinline__ void hlld(const R *VL, const R *VR, R *F, R &smax, R 
     R ptL = VL[PRS] + R(0.5) * (sq(VL[BX1]) + sq(VL[BX2]) + sq(VL[BX3]));
     R ptR = VR[PRS] + R(0.5) * (sq(VR[BX1]) + sq(VR[BX2]) + sq(VR[BX3]));
     R aL = (SL - uL) * VL[RHO], aR = (SR - uR) * VR[RHO];
-    R iden = R(1) / (aR - aL);
+    R iden = rcp(aR - aL);
     R SM = (aR * uR - aL * uL - ptR + ptL) * iden;
     R pts = (aR * ptL - aL * ptR + aL * aR * (uR - uL)) * iden;
 
@@ -484,13 +524,13 @@ __device__ __forceinline__ void hlld(const R *VL, const R *VR, R *F, R &smax, R 
         R pt = s ? ptR : ptL;
         R u = V[MX1 + n], rho = V[RHO];
         R Su = S - u, SSM = S - SM;
-        R iSSM = R(1) / SSM;
+        R iSSM = rcp(SSM);
         rs[s] = rho * Su * iSSM;
         R den = rho * Su * SSM - Bn2;
         R scale = rho * fabs(Su) * fabs(SSM) + Bn2;
         // degenerate case (S -> S_M with B_t -> 0): transverse values kept
         bool degen = fabs(den) <= R(sizeof(R) == 8 ? 1e-12 : 1e-6) * scale;
-        R iden2 = R(1) / den;
+        R iden2 = rcp(den);
         R fv = degen ? R(0) : Bn * (SM - u) * iden2;
         R fB = degen ? R(1) : (rho * Su * Su - Bn2) * iden2;
         vt[s] = V[MX1 + t] - V[BX1 + t] * fv;
@@ -515,7 +555,7 @@ __device__ __forceinline__ void hlld(const R *VL, const R *VR, R *F, R &smax, R 
 
     // double-star states
     R sB = sgn1(Bn);
-    R idn = R(1) / (sr[0] + sr[1]);
+    R idn = rcp(sr[0] + sr[1]);
     R vtt = (sr[0] * vt[0] + sr[1] * vt[1] + (Bt[1] - Bt[0]) * sB) * idn;
     R vbb = (sr[0] * vb[0] + sr[1] * vb[1] + (Bb[1] - Bb[0]) * sB) * idn;
     R Btt = (sr[0] * Bt[1] + sr[1] * Bt[0] + sr[0] * sr[1] * (vt[1] - vt[0]) * sB) * idn;
@@ -583,9 +623,9 @@ __device__ __forceinline__ void hllc(const R *VL, const R *VR, R *F, R &smax, R 
     phys_flux<D, PHYS_MHD>(VL, UL, FL, gam, ch, glm);
     phys_flux<D, PHYS_MHD>(VR, UR, FR, gam, ch, glm);
     // HLL averages (S_R U_R - S_L U_L - (F_R - F_L)) / (S_R - S_L)
-    const R id = R(1) / (SR - SL);
+    const R id = rcp(SR - SL);
     auto hav = [&](int q) { return (SR * UR[q] - SL * UL[q] - (FR[q] - FL[q])) * id; };
-    const R irh = R(1) / hav(RHO);
+    const R irh = rcp(hav(RHO));
     const R SM = hav(MX1 + n) * irh;
     const R vth = hav(MX1 + t) * irh, vbh = hav(MX1 + b) * irh;
     const R Bth = hav(BX1 + t), Bbh = hav(BX1 + b);
@@ -604,7 +644,7 @@ __device__ __forceinline__ void hllc(const R *VL, const R *VR, R *F, R &smax, R 
     }
     const R S = k ? SR : SL;
     const R u = Vk[MX1 + n], rho = Vk[RHO];
-    const R Su = S - u, iSSM = R(1) / (S - SM);
+    const R Su = S - u, iSSM = rcp(S - SM);
     const R pt = Vk[PRS] + R(0.5) * (sq(Vk[BX1]) + sq(Vk[BX2]) + sq(Vk[BX3]));
     const R pts = pt + rho * Su * (SM - u);
     const R vB = Vk[MX1] * Vk[BX1] + Vk[MX2] * Vk[BX2] + Vk[MX3] * Vk[BX3];
@@ -989,26 +1029,23 @@ template <typename R> __device__ __forceinline__ R minmod(R a, R b)
     }
 }
 
-// monotonised central limiter minmod((dp + dm)/2, 2 minmod(dp, dm)): for
-// differences of one sign, that sign times min(|dp + dm|/2, 2|dp|, 2|dm|).
+// half the monotonised central limiter minmod((dp + dm)/2, 2 minmod(dp, dm)):
+// for differences of one sign, that sign times min(|dp + dm|/4, |dp|, |dm|).
 // FP32 nests the medians (minmod of three = minmod(x, minmod(y, z)), and
-// doubling is exact): two v_med3_f32 in place of the sign test and selects.
-template <typename R> __device__ __forceinline__ R lim_mc(R dp, R dm)
-{
-    R c = R(0.5) * (dp + dm);
-    if constexpr (sizeof(R) == 4) {
-        return __builtin_amdgcn_fmed3f(c, 2.0f * __builtin_amdgcn_fmed3f(dp, dm, 0.0f), 0.0f);
-    } else {
-        R m = fmin(fmin(fabs(c), R(2) * fabs(dp)), R(2) * fabs(dm));
-        return (dp * dm > R(0)) ? copysign(m, c) : R(0);
-    }
-}
-
-// lim_mc(dp, dm) / 2 in FP32: the same medians on halved arguments
+// halving is exact): two v_med3_f32 in place of the sign test and selects.
+// FP64, which has no median, clamps the quarter sum to the interval from 0
+// to the difference of smaller magnitude: six minima and maxima in place of a
+// product, two comparisons and two-register selects.
 __device__ __forceinline__ float lim_mc_half(float dp, float dm)
 {
     return __builtin_amdgcn_fmed3f(0.25f * (dp + dm), __builtin_amdgcn_fmed3f(dp, dm, 0.0f), 0.0f);
 }
+__device__ __forceinline__ double lim_mc_half(double dp, double dm)
+{
+    const double lo = fmin(fmax(dp, dm), 0.0), hi = fmax(fmin(dp, dm), 0.0);
+    return fmax(fmin(0.25 * (dp + dm), hi), lo);
+}
+template <typename R> __device__ __forceinline__ R lim_mc(R dp, R dm) { return R(2) * lim_mc_half(dp, dm); }
 
 template <typename R> __device__ __forceinline__ R limiter(int lim, R dp, R dm)
 {
@@ -1032,22 +1069,10 @@ __device__ __forceinline__ void recon_offsets(const R *d, int lim, R dxr, R &dm,
         dp = R(0.5) * s;
         dm = -dp;
     } else if constexpr (RK == RK_PPM) {
-        R P, M;
-        if constexpr (sizeof(R) == 4) {
-            // half slopes lim_mc / 2 = med3((dp + dm)/4, minmod(dp, dm), 0) and
-            // 1/3 in place of 1/6: power-of-two scalings, so the same bits
-            R s0 = lim_mc_half(d[2], d[1]);
-            R sp = lim_mc_half(d[3], d[2]);
-            R sm = lim_mc_half(d[1], d[0]);
-            P = 0.5f * d[2] - (sp - s0) * (1.0f / 3.0f);   // Eq. ppm1, w_+ - w_0
-            M = -0.5f * d[1] + (sm - s0) * (1.0f / 3.0f);  // w_- - w_0
-        } else {
-            R s0 = lim_mc(d[2], d[1]);
-            R sp = lim_mc(d[3], d[2]);
-            R sm = lim_mc(d[1], d[0]);
-            P = R(0.5) * d[2] - (sp - s0) * R(1.0 / 6.0);   // Eq. ppm1, w_+ - w_0
-            M = -R(0.5) * d[1] + (sm - s0) * R(1.0 / 6.0);  // w_- - w_0
-        }
+        // half slopes and 1/3 in place of 1/6: power-of-two scalings, so the same bits
+        const R s0 = lim_mc_half(d[2], d[1]), sp = lim_mc_half(d[3], d[2]), sm = lim_mc_half(d[1], d[0]);
+        const R P = R(0.5) * d[2] - (sp - s0) * R(1.0 / 3.0);   // Eq. ppm1, w_+ - w_0
+        const R M = -R(0.5) * d[1] + (sm - s0) * R(1.0 / 3.0);  // w_- - w_0
         if constexpr (sizeof(R) == 4) {
             // Eq. ppm_parabolic_lim as medians: where P and M share a sign, -2M
             // and -2P have the other one and the median is 0; otherwise it is
@@ -1064,19 +1089,26 @@ __device__ __forceinline__ void recon_offsets(const R *d, int lim, R dxr, R &dm,
     } else {
         R a = d[2], c = d[1];                              // Delta w_{+1/2}, Delta w_{-1/2}
         R num = sq(a - c);
-        R ap = R(1) + num / (dxr * dxr + a * a);            // Eq. WENO3a
-        R am = R(1) + num / (dxr * dxr + c * c);
-        dp = (ap * a + R(0.5) * am * c) / (R(2) * ap + am); // Eq. WENO3
-        dm = -(am * c + R(0.5) * ap * a) / (R(2) * am + ap);
+        R ap = R(1) + quot(num, dxr * dxr + a * a);         // Eq. WENO3a
+        R am = R(1) + quot(num, dxr * dxr + c * c);
+        dp = quot(ap * a + R(0.5) * am * c, R(2) * ap + am); // Eq. WENO3
+        dm = -quot(am * c + R(0.5) * ap * a, R(2) * am + ap);
     }
 }
 
 // Upwind tracing of one wave (Eq. wnorm_predp/m) in offset form: returns
-// w*_{+-} - w_0.
+// w*_{+-} - w_0.  With the face values as reference states the upwind weight
+// multiplies nu alone: a wave that does not reach the face has nu cut to 0.
 template <typename R>
 __device__ __forceinline__ void trace(int wref, R dm, R dp, R nu, R numax, R numin, R &sm, R &sp)
 {
     R dw = dp - dm, d2 = dp + dm;
+    if (wref == WREF_FACE) {
+        const R h = R(0.5) * nu;
+        sp = dp - fmax(h, R(0)) * (dw + d2 * (R(3) - R(2) * nu));
+        sm = dm - fmin(h, R(0)) * (dw - d2 * (R(3) + R(2) * nu));
+        return;
+    }
     // upwind weights (1 + sgn nu)/2 and (1 - sgn nu)/2
     R bp = (nu > R(0)) ? R(1) : ((nu < R(0)) ? R(0) : R(0.5));
     R bm = R(1) - bp;
@@ -1086,12 +1118,9 @@ __device__ __forceinline__ void trace(int wref, R dm, R dp, R nu, R numax, R num
     if (wref == WREF_CELL) {
         rp = R(0);
         rm = R(0);
-    } else if (wref == WREF_CW84) {
+    } else {
         rp = dp - R(0.5) * numax * (dw + d2 * (R(3) - R(2) * numax));
         rm = dm - R(0.5) * numin * (dw - d2 * (R(3) + R(2) * numin));
-    } else {
-        rp = dp;
-        rm = dm;
     }
     sp = rp + bp * (tp - rp);
     sm = rm + bm * (tm - rm);
@@ -1122,8 +1151,8 @@ template <int D, typename R> __device__ __forceinline__ void eigen_setup(const R
     R bt2 = Bt2 * ir;
     R b2 = bn2 + bt2;
     R dab = a2 - b2;
-    R root = sqrt(dab * dab + R(4) * a2 * bt2);  // c_f^2 - c_s^2, exact for b_t = 0
-    R cf2 = R(0.5) * (a2 + b2 + root);
+    R rt = root(dab * dab + R(4) * a2 * bt2);  // c_f^2 - c_s^2, exact for b_t = 0
+    R cf2 = R(0.5) * (a2 + b2 + rt);
     R ia = rsq(a2), icf = rsq(cf2);
     e.rho = rho;
     e.srho = rho * isr;
@@ -1135,11 +1164,11 @@ template <int D, typename R> __device__ __forceinline__ void eigen_setup(const R
     e.ca = fabs(Bn) * isr;
     e.cs = e.a * e.ca * icf;                     // c_f c_s = a c_a
     R cs2 = e.cs * e.cs;
-    if (root > R(0)) {
-        R ir2 = R(0.5) / root;
-        R af2 = (root + dab) * ir2, as2 = (root - dab) * ir2;
-        e.af = sqrt(af2 > R(0) ? af2 : R(0));
-        e.as = sqrt(as2 > R(0) ? as2 : R(0));
+    if (rt > R(0)) {
+        R ir2 = R(0.5) * rcp(rt);
+        R af2 = (rt + dab) * ir2, as2 = (rt - dab) * ir2;
+        e.af = root(af2 > R(0) ? af2 : R(0));
+        e.as = root(as2 > R(0) ? as2 : R(0));
     } else {
         e.af = R(1);
         e.as = R(0);
@@ -1154,7 +1183,7 @@ template <int D, typename R> __device__ __forceinline__ void eigen_setup(const R
     }
     e.s = sgn1(Bn);
     R N = e.af * e.af * cf2 + e.as * e.as * cs2;
-    e.X = R(0.5) / N;
+    e.X = R(0.5) * rcp(N);
     e.Y = R(0.5) * ia * isr;
     e.Z = R(0.5) * ir * e.ia2;
 }
