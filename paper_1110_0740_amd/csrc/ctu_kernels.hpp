@@ -1297,9 +1297,10 @@ __global__ __launch_bounds__(NT) void k_mtT(MtArgs<R> a)
 // the cells lo-1 .. lo+n (n+2 positions s = 0 .. n+1).  Items are processed
 // in rounds of NT: each item computes its cell's normal predictor and
 // corner-coupled states; the left state of the face below the item comes
-// from the item DEL places earlier (in LDS, or carried over from the
-// previous round); the update of a cell waits for the round holding the
-// face above it.  DEL = 1 along x (pencils laid end to end), 64 across
+// from the item DEL places earlier (in LDS: this round's half of the slots,
+// or the end of the last round's); the update of a cell waits for the round
+// holding the face above it.  Two barriers a round: one half of the slots is
+// written while the other still serves the last round's readers.  DEL = 1 along x (pencils laid end to end), 64 across
 // (64 transverse positions per row, x fastest for coalescing).
 // ---------------------------------------------------------------------------
 
@@ -1354,12 +1355,11 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
 {
     constexpr int SHK = (VAR == VAR_SHOCK);
     constexpr int DEL = (D == 0) ? 1 : 64;
-    __shared__ R sP[NV][NT];
-    __shared__ R sF[NV][NT];
-    __shared__ R sL[NT];
-    __shared__ R cP[NV][DEL];
-    __shared__ R cF[NV][DEL];
-    __shared__ R cL[DEL];
+    // plus states, fluxes and signal speeds of this round and the last one,
+    // the two halves taken in turn
+    __shared__ R sP[NV][2 * NT];
+    __shared__ R sF[NV][2 * NT];
+    __shared__ R sL[2 * NT];
     __shared__ double red[NT / 64];
 
     const int tid = threadIdx.x;
@@ -1430,7 +1430,11 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
             pos = pos0;
         }
     }
-    for (int base = 0; base < items; base += NT) {
+    // LDS slots of the item and of the item DEL places before it (in this
+    // round's half, or at the end of the last round's); both change halves
+    // every round
+    int own = tid, left = (tid >= DEL) ? tid - DEL : 2 * NT - DEL + tid;
+    for (int base = 0; base < items; base += NT, own ^= NT, left ^= NT) {
         const int kit = base + tid;
         bool valid = kit < items;
         if (D == 0) {
@@ -1514,15 +1518,15 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
                 Up[q] += tr[q];
             }
 #pragma unroll
-            for (int q = 0; q < NV; q++) sP[q][tid] = Up[q];
+            for (int q = 0; q < NV; q++) sP[q][own] = Up[q];
         }
         __syncthreads();
 
         // ---- time-centred Riemann solve on the face below the item ----
         if (valid && s >= sface) {
-            R UL[NV], VL[NV], VR[NV], F[NV];
+            R UL[NV], VL[NV], VR[NV];
 #pragma unroll
-            for (int q = 0; q < NV; q++) UL[q] = (tid >= DEL) ? sP[q][tid - DEL] : cP[q][tid];
+            for (int q = 0; q < NV; q++) UL[q] = sP[q][left];
             int fL = c2p<PHYS>(UL, VL, gam, Wc);
             int fR = c2p<PHYS>(Um, VR, gam, Wc);
             fl |= fL | fR;
@@ -1536,7 +1540,6 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
                 for (int q = 0; q < NV; q++) VR[q] = bV.ld(q, c);
             }
             R pL = VL[PRS], pR = VR[PRS], rL = VL[RHO], rR = VR[RHO];
-            R smax = R(0);
             if (!o.hyp_off) {
                 // App. B: HLL on the faces of a flagged zone
                 if (SHK && ((fb[c - sD] | fb[c]) & FLAG_HLL))
@@ -1555,6 +1558,7 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
             // ---- flux registers: dt * A * (F - Pi) on listed faces ----
             if (a.reg && bx.reg1 > bx.reg0 && s >= r0) {
                 int gt0 = bx.lo[T0] + tc0, gt1 = (T1 < dim) ? bx.lo[T1] + tc1 : 0;
+        R F[NV], smax = R(0);
                 // only the rectangles on this face plane
                 const int *rf = a.rface + bx.rface[D] + (s - 1);
                 const int r0 = rf[0], r1 = rf[1];
@@ -1573,22 +1577,19 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
                 }
             }
 #pragma unroll
-            for (int q = 0; q < NV; q++) sF[q][tid] = F[q];
-            sL[tid] = smax;
+            for (int q = 0; q < NV; q++) sF[q][own] = F[q];
+            sL[own] = smax;
         }
         __syncthreads();
 
         // ---- conservative update (Eq. update) of the cell below the item ----
         if (valid && s >= supd) {
             const int cu = c - sD;
-            R lamc = fmax(sL[tid], (tid >= DEL) ? sL[tid - DEL] : cL[tid]) * idxD;
+            R lamc = fmax(smax, sL[left]) * idxD;
             R u[NV];
             const Blk<R> bUb = a.first ? bU : bUo;
 #pragma unroll
-            for (int q = 0; q < NV; q++) {
-                R Flo = (tid >= DEL) ? sF[q][tid - DEL] : cF[q][tid];
-                u[q] = bUb.ld(q, cu) - dtdx * (sF[q][tid] - Flo);
-            }
+            for (int q = 0; q < NV; q++) u[q] = bUb.ld(q, cu) - dtdx * (F[q] - sF[q][left]);
             R lamt = lamc;
             if (o.parab) {
                 R *lp = a.lam + bx.woff / NV + cu;
@@ -1630,18 +1631,9 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
             for (int q = 0; q < NV; q++) bUo.st(q, cu, u[q]);
         }
         count_fails(s >= r0 ? fl : 0, a.fails);
-        __syncthreads();
-        // ---- carry the last DEL items into the next round ----
-        if (tid >= NT - DEL) {
-            int ct = tid - (NT - DEL);
-#pragma unroll
-            for (int q = 0; q < NV; q++) {
-                cP[q][ct] = sP[q][tid];
-                cF[q][ct] = sF[q][tid];
-            }
-            cL[ct] = sL[tid];
-        }
-        __syncthreads();
+        // no barrier here: the next round writes the other halves, whose last
+        // readers are past this round's second barrier (plus states) or reach
+        // the next one's first before anything is written (fluxes)
     }
     double rb = ldexp(block_max(rate_loc, red), -bx.lshift);
     if (tid == 0 && a.rate) atomic_max_pos(a.rate, rb);
