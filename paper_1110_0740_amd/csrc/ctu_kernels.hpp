@@ -1523,6 +1523,7 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
         __syncthreads();
 
         // ---- time-centred Riemann solve on the face below the item ----
+        R F[NV], smax = R(0);
         if (valid && s >= sface) {
             R UL[NV], VL[NV], VR[NV];
 #pragma unroll
@@ -1558,7 +1559,6 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
             // ---- flux registers: dt * A * (F - Pi) on listed faces ----
             if (a.reg && bx.reg1 > bx.reg0 && s >= r0) {
                 int gt0 = bx.lo[T0] + tc0, gt1 = (T1 < dim) ? bx.lo[T1] + tc1 : 0;
-        R F[NV], smax = R(0);
                 // only the rectangles on this face plane
                 const int *rf = a.rface + bx.rface[D] + (s - 1);
                 const int r0 = rf[0], r1 = rf[1];
