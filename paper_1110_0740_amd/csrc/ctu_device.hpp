@@ -490,19 +490,26 @@ __device__ __forceinline__ void rusanov(const R *VL, const R *VR, R *F, R &smax,
 // HLLD (Miyoshi & Kusano 2005) for states sharing the normal field.
 //
 // Evaluated without branches, so that the lanes of a wave never split over the
-// five regions: the star values of both sides are formed, the state X that
-// holds the interface (outer, single or double star of side k) is selected
-// component by component, and the flux is the physical flux of X with X's
-// total pressure.  That equals F_k + S_k (U*_k - U_k) [+ S*_k (U**_k - U*_k)] by
-// the jump conditions that define the star states, and needs neither the outer
-// fluxes nor the conserved states of both sides: the FP32 t^n kernel, four
-// such solves per cell and plane, went from 1952 to 1409 instructions.  In
-// the degenerate case (S -> S_M with B_t -> 0) the star keeps the transverse
+// five regions: the star values of both sides are formed and the region that
+// holds the interface is chosen by selects.  Quantities of regions not
+// selected may be non-finite; they enter only through selects.
+//
+// FP32 (hlld_fan) forms the flux as F_k + S_k (U*_k - U_k) [+ S*_k (U**_k -
+// U*_k)].  FP64 (hlld_state) selects the state X at the interface (outer,
+// single or double star of side k) and takes the physical flux of X with X's
+// total pressure, which equals that by the jump conditions that define the
+// star states, and needs neither the outer fluxes nor the conserved states of
+// both sides nor the selects between them: the FP64 t^n kernel, four solves
+// per cell and plane, went from 2490 to 2128 instructions (192^3: 800 -> 775
+// us).  It rounds differently (1e-16); FP32 keeps its form, 1952 instructions
+// against 1645, because its t^n kernel is bound by its stores at size and the
+// rates, and with them the time steps, of FP32 runs stay the same to the bit.
+//
+// In the degenerate case (S -> S_M with B_t -> 0) the star keeps the transverse
 // field, which breaks the jump condition of the induction rows; they take u_k
-// in place of S_M there.  Quantities of regions not selected may be
-// non-finite; they enter only through selects.
+// in place of S_M there (hlld_state).
 template <int D, typename R>
-__device__ __forceinline__ void hlld(const R *VL, const R *VR, R *F, R &smax, R gam, R ch, int glm)
+__device__ __forceinline__ void hlld_state(const R *VL, const R *VR, R *F, R &smax, R gam, R ch, int glm)
 {
     constexpr int n = Ax<D>::n, t = Ax<D>::t, b = Ax<D>::b;
     const R Bn = VL[BX1 + n], Bn2 = Bn * Bn;
@@ -599,6 +606,118 @@ __device__ __forceinline__ void hlld(const R *VL, const R *VR, R *F, R &smax, R 
     F[ENG] = (EX + pX) * u - vBX * Bn;
     F[BX1 + t] = u * BtX - Bn * vtX + du * Vk[BX1 + t];
     F[BX1 + b] = u * BbX - Bn * vbX + du * Vk[BX1 + b];
+}
+
+template <int D, typename R>
+__device__ __forceinline__ void hlld_fan(const R *VL, const R *VR, R *F, R &smax, R gam, R ch, int glm)
+{
+    constexpr int n = Ax<D>::n, t = Ax<D>::t, b = Ax<D>::b;
+    R cfL = cfast_mhd<D>(VL, gam), cfR = cfast_mhd<D>(VR, gam);
+    R uL = VL[MX1 + n], uR = VR[MX1 + n];
+    R SL = fmin(uL - cfL, uR - cfR);
+    R SR = fmax(uL + cfL, uR + cfR);
+    smax = fmax(fabs(SL), fabs(SR));
+    R UL[NV], UR[NV], FL[NV], FR[NV];
+    phys_flux<D, PHYS_MHD>(VL, UL, FL, gam, ch, glm);
+    phys_flux<D, PHYS_MHD>(VR, UR, FR, gam, ch, glm);
+    const R Bn = VL[BX1 + n];
+    const R Bn2 = Bn * Bn;
+    R ptL = VL[PRS] + R(0.5) * (sq(VL[BX1]) + sq(VL[BX2]) + sq(VL[BX3]));
+    R ptR = VR[PRS] + R(0.5) * (sq(VR[BX1]) + sq(VR[BX2]) + sq(VR[BX3]));
+    R aL = (SL - uL) * VL[RHO], aR = (SR - uR) * VR[RHO];
+    R iden = rcp(aR - aL);
+    R SM = (aR * uR - aL * uL - ptR + ptL) * iden;
+    R pts = (aR * ptL - aL * ptR + aL * aR * (uR - uL)) * iden;
+
+    // single-star states; index 0 = left, 1 = right
+    R rs[2], vt[2], vb[2], Bt[2], Bb[2], Es[2], sr[2], isr[2];
+#pragma unroll
+    for (int s = 0; s < 2; s++) {
+        const R *V = s ? VR : VL;
+        const R *U = s ? UR : UL;
+        R S = s ? SR : SL;
+        R pt = s ? ptR : ptL;
+        R u = V[MX1 + n], rho = V[RHO];
+        R Su = S - u, SSM = S - SM;
+        R iSSM = rcp(SSM);
+        rs[s] = rho * Su * iSSM;
+        R den = rho * Su * SSM - Bn2;
+        R scale = rho * fabs(Su) * fabs(SSM) + Bn2;
+        // degenerate case (S -> S_M with B_t -> 0): transverse values kept
+        bool degen = fabs(den) <= R(sizeof(R) == 8 ? 1e-12 : 1e-6) * scale;
+        R iden2 = rcp(den);
+        R fv = degen ? R(0) : Bn * (SM - u) * iden2;
+        R fB = degen ? R(1) : (rho * Su * Su - Bn2) * iden2;
+        vt[s] = V[MX1 + t] - V[BX1 + t] * fv;
+        vb[s] = V[MX1 + b] - V[BX1 + b] * fv;
+        Bt[s] = V[BX1 + t] * fB;
+        Bb[s] = V[BX1 + b] * fB;
+        R vB = V[MX1] * V[BX1] + V[MX2] * V[BX2] + V[MX3] * V[BX3];
+        R vBs = SM * Bn + vt[s] * Bt[s] + vb[s] * Bb[s];
+        Es[s] = (Su * U[ENG] - pt * u + pts * SM + Bn * (vB - vBs)) * iSSM;
+        isr[s] = rsq(rs[s]);
+        sr[s] = rs[s] * isr[s];
+    }
+    R SLs = SM - fabs(Bn) * isr[0];
+    R SRs = SM + fabs(Bn) * isr[1];
+
+    // region: outer (F_L or F_R), single star (L* or R*) or double star on
+    // side k; k follows S_M inside the fan
+    const bool outerL = SL >= R(0), outerR = SR <= R(0);
+    const bool outer = outerL || outerR;
+    const bool single = (SLs >= R(0)) || (SRs <= R(0));
+    const bool k = outerL ? false : (outerR ? true : !(SM >= R(0)));
+
+    // double-star states
+    R sB = sgn1(Bn);
+    R idn = rcp(sr[0] + sr[1]);
+    R vtt = (sr[0] * vt[0] + sr[1] * vt[1] + (Bt[1] - Bt[0]) * sB) * idn;
+    R vbb = (sr[0] * vb[0] + sr[1] * vb[1] + (Bb[1] - Bb[0]) * sB) * idn;
+    R Btt = (sr[0] * Bt[1] + sr[1] * Bt[0] + sr[0] * sr[1] * (vt[1] - vt[0]) * sB) * idn;
+    R Bbb = (sr[0] * Bb[1] + sr[1] * Bb[0] + sr[0] * sr[1] * (vb[1] - vb[0]) * sB) * idn;
+    R vBss = SM * Bn + vtt * Btt + vbb * Bbb;
+
+    // star and double-star states of side k
+    const R rk = k ? rs[1] : rs[0], vtk = k ? vt[1] : vt[0], vbk = k ? vb[1] : vb[0];
+    const R Btk = k ? Bt[1] : Bt[0], Bbk = k ? Bb[1] : Bb[0], Ek = k ? Es[1] : Es[0];
+    const R srk = k ? sr[1] : sr[0];
+    const R vBsk = SM * Bn + vtk * Btk + vbk * Bbk;
+    R Us[NV], Uss[NV];
+    Us[RHO] = rk;
+    Us[MX1 + n] = rk * SM;
+    Us[MX1 + t] = rk * vtk;
+    Us[MX1 + b] = rk * vbk;
+    Us[ENG] = Ek;
+    Us[BX1 + n] = Bn;
+    Us[BX1 + t] = Btk;
+    Us[BX1 + b] = Bbk;
+    Us[PSI] = k ? VR[PSI] : VL[PSI];
+    Uss[RHO] = rk;
+    Uss[MX1 + n] = rk * SM;
+    Uss[MX1 + t] = rk * vtt;
+    Uss[MX1 + b] = rk * vbb;
+    Uss[ENG] = Ek + (k ? R(1) : R(-1)) * srk * (vBsk - vBss) * sB;
+    Uss[BX1 + n] = Bn;
+    Uss[BX1 + t] = Btt;
+    Uss[BX1 + b] = Bbb;
+    Uss[PSI] = Us[PSI];
+    const R Sk = k ? SR : SL;
+    const R Sks = k ? SRs : SLs;
+#pragma unroll
+    for (int q = 0; q < NV; q++) {
+        R Fk = k ? FR[q] : FL[q];
+        R Uk = k ? UR[q] : UL[q];
+        R f1 = Fk + Sk * (Us[q] - Uk);       // single-star flux
+        R f2 = f1 + Sks * (Uss[q] - Us[q]);  // double-star flux
+        F[q] = outer ? Fk : (single ? f1 : f2);
+    }
+}
+
+template <int D, typename R>
+__device__ __forceinline__ void hlld(const R *VL, const R *VR, R *F, R &smax, R gam, R ch, int glm)
+{
+    if constexpr (sizeof(R) == 4) hlld_fan<D>(VL, VR, F, smax, gam, ch, glm);
+    else hlld_state<D>(VL, VR, F, smax, gam, ch, glm);
 }
 
 // HLLC for MHD (Sec. 3.1 lists it for both modules), the single-contact
