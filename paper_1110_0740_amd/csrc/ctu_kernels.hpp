@@ -61,7 +61,31 @@ struct KBox {
     int lshift;  // the box's level when the plan's dt is the level-0 step (one plan over
                  // several levels); 0 otherwise.  The box steps by dt / 2^lshift and
                  // reports its rate times 2^-lshift (the level-0 rate of its CFL number)
+    // layout of the T_d fields (see tidx): nine planes of tcells elements from
+    // element toff of the field
+    long long toff;
+    int tcells, tp, tpl, tF, tS, tHp;
+    int tnt;  // rows are whole lines: the t^n kernel stores them nontemporally
 };
+
+// T_d fields live on the region [g-1, g+n] only (positions rx, ry, rz from its
+// low corner) in an order of their own, in which every row of a t^n tile is
+// whole 128-byte lines that one block writes: row pitch tp and plane pitch tpl
+// are padded to lines, the columns from tF on (strip tiles) are stored
+// transposed, ry fastest with pitch tHp, from tS; boxes on the flat t^n layout
+// keep its position order (tp = n[0] + 3).  The padding is written too.  Rows
+// that start inside a line reached memory as partial lines: at 256^3 FP32 the
+// t^n kernel took 917 us with the ghosted row pitch (550 without its stores,
+// 1029 without its Riemann solves), 861 with this one, and 810 with
+// nontemporal stores, which leave more of the caches to the reads and which
+// on partial lines doubled its time; the x sweep after it 654 -> 629.  Every
+// layout fits the ghosted extent; where padded rows would not, rows keep the
+// region's width and ordinary stores.
+__device__ __forceinline__ int tidx(const KBox &bx, int rx, int ry, int rz)
+{
+    const int main = rz * bx.tpl + ry * bx.tp + rx, strip = bx.tS + (2 * rz + rx - bx.tF) * bx.tHp + ry;
+    return rx < bx.tF ? main : strip;
+}
 
 // the step of a box: the plan's dt, halved per level of a multi-level plan
 // (exact: a power-of-two scaling)
@@ -111,14 +135,15 @@ template <typename R> struct Blk {
         else
             return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(rs, vo, so, 0));
     }
-    __device__ __forceinline__ void st(int q, int e, R v) const
+    // AUX = 2: nontemporal
+    template <int AUX = 0> __device__ __forceinline__ void st(int q, int e, R v) const
     {
         const int vo = (int)((uint32_t)e * (uint32_t)sizeof(R)), so = (int)((uint32_t)q * pb);
         if constexpr (sizeof(R) == 4) {
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, vo, so, 0);
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, vo, so, AUX);
         } else {
             using W = decltype(__builtin_amdgcn_raw_buffer_load_b64(rs, 0, 0, 0));
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(W, v), rs, vo, so, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(W, v), rs, vo, so, AUX);
         }
     }
 };
@@ -802,23 +827,18 @@ template <typename R> __device__ __forceinline__ void ld_cell(const Blk<R> &bV, 
     for (int q = 0; q < NV; q++) V[q] = bV.ld(q, c);
 }
 
-// one face: the first-order flux G = F on the D-face below cell (i,j,k),
-// from states already in registers: VL of the cell below the face, VR of
-// cell (i,j,k).  Both are copied (the solver overwrites B_n) through an
+// one face: the first-order flux G = F on the D-face between cells cL and cR,
+// from their states VL and VR already in registers.  Both are copied (the solver overwrites B_n) through an
 // empty register barrier: a cell's state is shared by its three faces, and
 // without the barrier the compiler would share and contract their
 // arithmetic differently from a face solved alone, so the same face would
 // round differently under another launch shape
 template <int D, int PHYS, int RS, int SHK, typename R>
-__device__ __forceinline__ void tface_s(const R *VL_in, const R *VR_in, const KBox &bx, int i, int j, int k,
-                                        const KOpts &o, R gam, R ch, R *G, const unsigned char *fb)
+__device__ __forceinline__ void tface_s(const R *VL_in, const R *VR_in, int cL, int cR, const KOpts &o, R gam, R ch,
+                                        R *G, const unsigned char *fb)
 {
     bool hl = false;
-    if constexpr (SHK) {
-        int di, dj, dk;
-        unit<D>(di, dj, dk);
-        hl = ((fb[cidx(bx, i - di, j - dj, k - dk)] | fb[cidx(bx, i, j, k)]) & FLAG_HLL) != 0;
-    }
+    if constexpr (SHK) hl = ((fb[cL] | fb[cR]) & FLAG_HLL) != 0;
     R VL[NV], VR[NV];
 #pragma unroll
     for (int q = 0; q < NV; q++) {
@@ -845,13 +865,16 @@ __device__ __forceinline__ void tface_s(const R *VL_in, const R *VR_in, const KB
 #ifndef CTU_TC_WAVES_PAR_F64
 #define CTU_TC_WAVES_PAR_F64 2
 #endif
-template <int PAR, typename R> constexpr int tc_waves()
+// the FP32 fixed-option HLLD kernel needs 174 registers by itself; three waves
+// leave 168
+template <int PAR, int RS, int VAR, typename R> constexpr int tc_waves()
 {
+    if (!PAR && sizeof(R) == 4 && VAR == VAR_FAST && RS == RS_HLLD) return 3;
     return PAR ? (sizeof(R) == 4 ? CTU_TC_WAVES_PAR_F32 : CTU_TC_WAVES_PAR_F64) : 1;
 }
 
 template <int DIM, int PHYS, int RS, int PAR, int VAR, typename R>
-__global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a)
+__global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(TArgs<R> a)
 {
     constexpr int SHK = (VAR == VAR_SHOCK);
     constexpr int TX = TTile<DIM>::TX, TY = TTile<DIM>::TY;
@@ -876,7 +899,8 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a
     const R *Pf = PAR ? a.PF + (bx.woff / NV) * (NPF * DIM) : nullptr;
     const Blk<R> bV(Vb, bx.cells);
     const unsigned char *fb = SHK ? a.flag + bx.woff / NV : nullptr;
-    const Blk<R> bT0(a.T[0] + bx.woff, bx.cells), bT1(a.T[1] + bx.woff, bx.cells), bT2(DIM == 3 ? a.T[2] + bx.woff : Vb, bx.cells);
+    const Blk<R> bT0(a.T[0] + bx.toff, bx.tcells), bT1(a.T[1] + bx.toff, bx.tcells);
+    const Blk<R> bT2(DIM == 3 ? a.T[2] + bx.toff : Vb, bx.tcells);
     const R ix = R(1.0 / bx.dx[0]), iy = R(1.0 / bx.dx[1]), iz = R(1.0 / bx.dx[2]);
     const int hi0 = bx.g[0] + bx.n[0];                       // last region cell along x
     const int hi1 = (DIM == 3) ? bx.g[1] + bx.n[1] : 0;
@@ -886,6 +910,10 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a
     // below it sits at lx / ly, the faces above it at lx + 1 / ly + sy
     int i, j, lx, ly, sy;
     bool xf, yf, inplane;
+    // the lane's element of the T_d fields on the region's first plane, their
+    // step per plane, and whether the lane stores one (cells and the padding)
+    int tb, ts;
+    bool wr;
     // the extra face of this lane (if any): below position (ei, ej), along
     // x (ed = 0) or y (ed = 1), into slot es
     int ei = 0, ej = 0, ed = -1, es = 0;
@@ -899,6 +927,9 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a
         inplane = xf && yf;
         lx = ly = tid;
         sy = W1;
+        tb = p;
+        ts = bx.tpl;
+        wr = p < bx.tpl;
         if (et >= 0 && et <= W1) {
             const int q = tl.a + NT + (et < W1 ? et : 0), qx = q % W1, qy = q / W1;
             ei = bx.g[0] - 1 + qx;
@@ -927,6 +958,11 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a
         lx = ty * (tw + 1) + tx;
         ly = ty * tw + tx;
         sy = tw;
+        const int rx = tl.a + tx, ry = (DIM == 3) ? y0 + ty : 0;
+        tb = tidx(bx, rx, ry, 0);
+        const bool tr = rx >= bx.tF;  // in the transposed columns
+        ts = (DIM == 2) ? bx.tp : (tr ? 2 * bx.tHp : bx.tpl);
+        wr = pos && (tr ? ry < bx.tHp : rx < bx.tp && (DIM == 2 || ry < bx.n[1] + 2));
         if (e >= 0 && e < th) {
             ei = bx.g[0] - 1 + tl.a + tw;
             ej = (DIM == 3) ? bx.g[1] - 1 + y0 + e : 0;
@@ -944,11 +980,16 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a
     const int m0 = bx.g[AM] - 1 + tl.c;
     const int m1 = min(m0 + a.lm - 1, bx.g[AM] + bx.n[AM]);
 
+    // the lane's cell and its extra face's cell on plane 0, and the strides
+    // along y and the marching axis
+    const int sY = bx.N[0], sM = (DIM == 3) ? bx.N[0] * bx.N[1] : bx.N[0];
+    const int cb = (DIM == 3) ? cidx(bx, i, j, 0) : i, eb = (DIM == 3) ? cidx(bx, ei, ej, 0) : ei;
+
     // the lane's cell state on this plane (the right state of its three
     // faces) and on the previous one (the left state of the marching face),
     // loaded once and carried from plane to plane
     R Vc[NV], Vp[NV];
-    if (inplane) ld_cell(bV, cidx(bx, i, (DIM == 3) ? j : m0 - 1, (DIM == 3) ? m0 - 1 : 0), Vp);
+    if (inplane) ld_cell(bV, cb + (m0 - 1) * sM, Vp);
     R Gm_prev[NV], Lx_prev[NV], Ly_prev[NV];
     // the stored T_d and V^{n+1/2} values of the last finished cell, held
     // until the next cell's stores (see keep): FP32 parabolic runs, whose
@@ -964,13 +1005,13 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a
 #pragma unroll
     for (int q = 0; q < NKT; q++) Tk[q] = R(0);
     for (int m = m0; m <= m1 + 1; m++) {
-        const int cj = (DIM == 3) ? j : m, ck = (DIM == 3) ? m : 0;
+        const int c = cb + m * sM, ec = eb + m * sM;  // this plane's cells
         // U^n and P of the cell this plane finishes, loaded ahead of the face
         // solves that hide their latency (PRE)
         R Upre[NV], Ppre[7];
         if constexpr (PRE) {
             if (inplane && m > m0) {
-                const int pc = cidx(bx, i, (DIM == 3) ? j : m - 1, (DIM == 3) ? m - 1 : 0);
+                const int pc = c - sM;
 #pragma unroll
                 for (int q = 0; q < NV; q++) Upre[q] = Blk<R>(a.U + bx.uoff, bx.cells).ld(q, pc);
 #pragma unroll
@@ -984,22 +1025,18 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a
         constexpr bool GROUP = sizeof(R) == 4;
         constexpr bool GROUP_E = GROUP && !SHK && RS != RS_ROE;
         R VLx[NV], VLy[NV], VLe[NV], VRe[NV];
-        if (inplane || (m <= m1 && (xf || yf))) ld_cell(bV, cidx(bx, i, cj, ck), Vc);
+        if (inplane || (m <= m1 && (xf || yf))) ld_cell(bV, c, Vc);
         if constexpr (GROUP) {
-            if (m <= m1 && xf) ld_cell(bV, cidx(bx, i - 1, cj, ck), VLx);
+            if (m <= m1 && xf) ld_cell(bV, c - 1, VLx);
             if constexpr (DIM == 3)
-                if (m <= m1 && yf) ld_cell(bV, cidx(bx, i, j - 1, ck), VLy);
+                if (m <= m1 && yf) ld_cell(bV, c - sY, VLy);
             // and the two states of the lane's extra face, where the registers
             // they take keep three waves per SIMD (not with shock flags or the
             // Roe solver)
             if constexpr (GROUP_E) {
-                if (m <= m1 && ed == 0) {
-                    const int ej2 = (DIM == 3) ? ej : m;
-                    ld_cell(bV, cidx(bx, ei - 1, ej2, ck), VLe);
-                    ld_cell(bV, cidx(bx, ei, ej2, ck), VRe);
-                } else if (DIM == 3 && m <= m1 && ed == 1) {
-                    ld_cell(bV, cidx(bx, ei, ej - 1, m), VLe);
-                    ld_cell(bV, cidx(bx, ei, ej, m), VRe);
+                if (m <= m1 && ed >= 0) {
+                    ld_cell(bV, ec - ((DIM == 3 && ed == 1) ? sY : 1), VLe);
+                    ld_cell(bV, ec, VRe);
                 }
             }
         }
@@ -1007,49 +1044,49 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a
         // and the in-plane low faces of every position whose face borders the
         // region ----
         R Gm[NV];
-        if (inplane) tface_s<AM, PHYS, RS, SHK>(Vp, Vc, bx, i, cj, ck, o, gam, ch, Gm, fb);
+        if (inplane) tface_s<AM, PHYS, RS, SHK>(Vp, Vc, c - sM, c, o, gam, ch, Gm, fb);
         if (m <= m1) {
             R G[NV];
             if (xf) {
-                if constexpr (!GROUP) ld_cell(bV, cidx(bx, i - 1, cj, ck), VLx);
-                tface_s<0, PHYS, RS, SHK>(VLx, Vc, bx, i, cj, ck, o, gam, ch, G, fb);
+                if constexpr (!GROUP) ld_cell(bV, c - 1, VLx);
+                tface_s<0, PHYS, RS, SHK>(VLx, Vc, c - 1, c, o, gam, ch, G, fb);
 #pragma unroll
                 for (int q = 0; q < NV; q++) Gx[q][lx] = G[q];
             }
             if constexpr (DIM == 3) {
                 if (yf) {
-                    if constexpr (!GROUP) ld_cell(bV, cidx(bx, i, j - 1, ck), VLy);
-                    tface_s<1, PHYS, RS, SHK>(VLy, Vc, bx, i, cj, ck, o, gam, ch, G, fb);
+                    if constexpr (!GROUP) ld_cell(bV, c - sY, VLy);
+                    tface_s<1, PHYS, RS, SHK>(VLy, Vc, c - sY, c, o, gam, ch, G, fb);
 #pragma unroll
                     for (int q = 0; q < NV; q++) Gy[q][ly] = G[q];
                 }
             }
             // the extra faces
             if (ed == 0) {
-                const int ej2 = (DIM == 3) ? ej : m;
                 if constexpr (!GROUP_E) {
-                    ld_cell(bV, cidx(bx, ei - 1, ej2, ck), VLe);
-                    ld_cell(bV, cidx(bx, ei, ej2, ck), VRe);
+                    ld_cell(bV, ec - 1, VLe);
+                    ld_cell(bV, ec, VRe);
                 }
-                tface_s<0, PHYS, RS, SHK>(VLe, VRe, bx, ei, ej2, ck, o, gam, ch, G, fb);
+                tface_s<0, PHYS, RS, SHK>(VLe, VRe, ec - 1, ec, o, gam, ch, G, fb);
 #pragma unroll
                 for (int q = 0; q < NV; q++) Gx[q][es] = G[q];
             } else if (DIM == 3 && ed == 1) {
                 if constexpr (!GROUP_E) {
-                    ld_cell(bV, cidx(bx, ei, ej - 1, m), VLe);
-                    ld_cell(bV, cidx(bx, ei, ej, m), VRe);
+                    ld_cell(bV, ec - sY, VLe);
+                    ld_cell(bV, ec, VRe);
                 }
-                tface_s<(DIM == 3 ? 1 : 0), PHYS, RS, SHK>(VLe, VRe, bx, ei, ej, m, o, gam, ch, G, fb);
+                tface_s<(DIM == 3 ? 1 : 0), PHYS, RS, SHK>(VLe, VRe, ec - sY, ec, o, gam, ch, G, fb);
 #pragma unroll
                 for (int q = 0; q < NV; q++) Gy[q][es] = G[q];
             }
         }
         __syncthreads();
-        if (inplane) {
+        // lanes that only store padding (wr without inplane) run on with
+        // whatever their registers and slots hold
+        if (wr) {
             // ---- finish the previous plane (its high marching face is Gm) ----
             if (m > m0) {
-                const int pj = (DIM == 3) ? j : m - 1, pk = (DIM == 3) ? m - 1 : 0;
-                const int c = cidx(bx, i, pj, pk);
+                const int pc = c - sM, ct = tb + (m - bx.g[AM]) * ts;
                 const R im = (DIM == 3) ? iz : iy;
                 // parabolic runs: the divergence P of Pi^n (k_pdiv), which
                 // enters every T_d and the half step in full (Eq. transv: the
@@ -1060,7 +1097,7 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a
                     Pd[RHO] = R(0);
                     Pd[PSI] = R(0);
 #pragma unroll
-                    for (int q = 0; q < 7; q++) Pd[MX1 + q] = PRE ? Ppre[q] : Pf[q * cs + c];
+                    for (int q = 0; q < 7; q++) Pd[MX1 + q] = PRE ? Ppre[q] : (inplane ? Pf[q * cs + pc] : R(0));
                 }
                 auto addp = [&](R x, int q) -> R {
                     if constexpr (PAR) return x + Pd[q];
@@ -1070,6 +1107,17 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a
 #pragma unroll
                     for (int q = 0; q < NKT; q++) keep(Tk[q]);
                 }
+                auto store_t = [&](int q, R t0, R t1, R t2) {
+                    if (bx.tnt) {
+                        bT0.template st<2>(q, ct, t0);
+                        bT1.template st<2>(q, ct, t1);
+                        if constexpr (DIM == 3) bT2.template st<2>(q, ct, t2);
+                    } else {
+                        bT0.st(q, ct, t0);
+                        bT1.st(q, ct, t1);
+                        if constexpr (DIM == 3) bT2.st(q, ct, t2);
+                    }
+                };
                 R Lm[NV], S[NV];
 #pragma unroll
                 for (int q = 0; q < NV; q++) {
@@ -1089,20 +1137,25 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, R>())) void k_tcouple(TArgs<R> a
                         Tk[q] = t0;
                         Tk[NV + q] = t1;
                         if constexpr (DIM == 3) Tk[2 * NV + q] = t2;
+                    } else {
+                        store_t(q, t0, t1, t2);
                     }
-                    bT0.st(q, c, t0);
-                    bT1.st(q, c, t1);
-                    if constexpr (DIM == 3) bT2.st(q, c, t2);
+                }
+                if constexpr (KEEPT) {
+                    // after the loop: its arithmetic stays one basic block
+#pragma unroll
+                    for (int q = 0; q < NV; q++)
+                        store_t(q, Tk[q], Tk[NV + q], Tk[(DIM == 3 ? 2 * NV : 0) + q]);
                 }
                 if constexpr (PAR) {
                     R u[NV], v[NV];
 #pragma unroll
-                    for (int q = 0; q < NV; q++) u[q] = (PRE ? Upre[q] : Blk<R>(a.U + bx.uoff, bx.cells).ld(q, c)) + hdt * S[q];
+                    for (int q = 0; q < NV; q++) u[q] = (PRE ? Upre[q] : Blk<R>(a.U + bx.uoff, bx.cells).ld(q, pc)) + hdt * S[q];
                     c2p<PHYS_MHD>(u, v, gam);
 #pragma unroll
                     for (int q = 0; q < NV; q++) {
                         if constexpr (KEEPT) Tk[DIM * NV + q] = v[q];
-                        Blk<R>(a.Vh + bx.woff, bx.cells).st(q, c, v[q]);
+                        if (inplane) Blk<R>(a.Vh + bx.woff, bx.cells).st(q, pc, v[q]);
                     }
                 }
             }
@@ -1279,13 +1332,14 @@ __global__ __launch_bounds__(NT) void k_mtT(MtArgs<R> a)
 #pragma unroll
     for (int d = 0; d < DIM; d++) {
         if (!need[d]) continue;
-        const Blk<R> bT(a.T[d] + bx.woff, bx.cells);
+        const Blk<R> bT(a.T[d] + bx.toff, bx.tcells);
+        const int ct = tidx(bx, cc[0] - bx.g[0] + 1, cc[1] - bx.g[1] + 1, DIM == 3 ? cc[2] - bx.g[2] + 1 : 0);
 #pragma unroll
         for (int q = 0; q < NV; q++) {
             R t;
             if constexpr (DIM == 3) t = (d == 0) ? L[1][q] + L[2][q] : ((d == 1) ? L[0][q] + L[2][q] : L[0][q] + L[1][q]);
             else t = (d == 0) ? L[1][q] : L[0][q];
-            bT.st(q, c, t);
+            bT.st(q, ct, t);
         }
     }
 }
@@ -1407,7 +1461,7 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
     int di, dj, dk;
     unit<D>(di, dj, dk);
     const Blk<R> bV(a.V + bx.woff, bx.cells), bU(a.U + bx.uoff, bx.cells), bUo(a.Uout + bx.uoff, bx.cells);
-    const Blk<R> bT(a.T[D] + bx.woff, bx.cells);
+    const Blk<R> bT(a.T[D] + bx.toff, bx.tcells);
     const unsigned char *fb = SHK ? a.flag + bx.woff / NV : nullptr;
     double rate_loc = 0.0, dpp_loc = 0.0;
     // last sweep: the cooling exponent 1 - beta and the floor's T^(1-beta);
@@ -1463,6 +1517,7 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
         if (D == 1) { ci = bx.g[0] + tc0; cj = cD; ck = bx.g[2] + tc1; }
         if (D == 2) { ci = bx.g[0] + tc0; cj = bx.g[1] + tc1; ck = cD; }
         const int c = valid ? cidx(bx, ci, cj, ck) : 0;
+        const int ct = tidx(bx, ci - bx.g[0] + 1, cj - bx.g[1] + 1, dim == 3 ? ck - bx.g[2] + 1 : 0);
         const int sD = (D == 0) ? 1 : (D == 1 ? bx.N[0] : bx.N[0] * bx.N[1]);
 
         R Um[NV];
@@ -1484,7 +1539,7 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
             R tr[NV];
             if constexpr (TPRE) {
 #pragma unroll
-                for (int q = 0; q < NV; q++) tr[q] = bT.ld(q, c);
+                for (int q = 0; q < NV; q++) tr[q] = bT.ld(q, ct);
             }
             R Vm[NV], Vp[NV];
             Wc = w_guess<PHYS>(Vs[2], gam);
@@ -1507,7 +1562,7 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
             R Up[NV];
             if constexpr (!TPRE) {
 #pragma unroll
-                for (int q = 0; q < NV; q++) tr[q] = bT.ld(q, c);
+                for (int q = 0; q < NV; q++) tr[q] = bT.ld(q, ct);
             }
             p2c<PHYS>(Vm, Um, gam);
             p2c<PHYS>(Vp, Up, gam);

@@ -363,7 +363,9 @@ ctu_plan::Split auto_split(const ctu_plan *p)
         for (int r : { 62, 46, 30, 22, 18, 14, 10, 6, 2 }) cand.push_back(r);  // rows + 2 in whole rounds
         s.rows[D] = pick([&](int v) { return row_cost(p, D, v); }, cand).first;
     }
-    const auto xp = pick([&](int v) { return x_pencil_cost(p, v); }, { 16, 32, 8, 64, 4, 2, 1 });
+    std::vector<int> pencils = { 16, 32, 8, 64 };
+    for (int P = 1; P < 64; P++) pencils.push_back(P);
+    const auto xp = pick([&](int v) { return x_pencil_cost(p, v); }, pencils);
     const auto xr = pick([&](int v) { return row_cost(p, 0, v); }, { 1022, 510, 254, 190, 126, 62, 30 });
     s.xp = xp.first;
     if (xr.second < 0.95 * xp.second) s.xrows = xr.first;
@@ -414,6 +416,53 @@ void shape_capacity(const ctu_plan *p, size_t cap[4])
     }
 }
 
+// The T_d layout of every box (see tidx) under the plan's shape, each with at
+// most the box's ghosted elements; rows keep the region's own width where
+// padding them to lines would not fit.
+void build_t_layout(ctu_plan *p)
+{
+    const long long line = 128 / p->esize;
+    auto up = [&](long long v) { return (v + line - 1) / line * line; };
+    long long off = 0;
+    for (KBox &bx : p->hboxes) {
+        const bool d3 = p->opts.dim == 3;
+        const long long W = bx.n[0] + 2, H = bx.n[1] + 2, D = d3 ? bx.n[2] + 2 : 1;
+        bx.tF = INT32_MAX;
+        bx.tS = 0;
+        bx.tHp = 0;
+        long long total;
+        auto set = [&](long long tp, long long tpl) {
+            bx.tp = (int)tp;
+            bx.tpl = (int)tpl;
+            total = tpl * D;
+        };
+        if (d3 && use_flat(p, bx)) {
+            set(W + 1, up((W + 1) * H));
+        } else if (d3 && rect_full_width((int)W) < W) {
+            const long long F = rect_full_width((int)W);
+            set(F, F * H);
+            bx.tF = (int)F;
+            bx.tS = (int)total;
+            bx.tHp = (int)up(H);
+            total += 2 * up(H) * D;
+        } else {
+            set(up(W), up(W) * H);
+        }
+        bx.tnt = 1;
+        if (up(total) > bx.cells) {
+            bx.tnt = 0;
+            bx.tF = INT32_MAX;
+            bx.tS = bx.tHp = 0;
+            if (d3 && use_flat(p, bx)) set(W + 1, (W + 1) * H);
+            else set(W, W * H);
+        }
+        bx.tcells = (int)(up(total) <= bx.cells ? up(total) : total);
+        bx.toff = off;
+        if (off % line != 0) bx.tnt = 0;
+        off += NV * (long long)bx.tcells;
+    }
+}
+
 // the tables that depend on the launch shape: t^n tiles and sweep columns,
 // rebuilt on the host and copied into the buffers reserved at creation
 ctu_status build_shape_tables(ctu_plan *p)
@@ -422,6 +471,7 @@ ctu_status build_shape_tables(ctu_plan *p)
     p->t_tc.h.clear();
     for (int D = 0; D < 3; D++) p->t_sweep[D].h.clear();
     resolve_split(p);
+    build_t_layout(p);
     const ctu_plan::Split &sp = p->split;
     const int LM = sp.lm;
     for (int b = 0; b < (int)p->hboxes.size(); b++) {
@@ -487,6 +537,7 @@ ctu_status build_shape_tables(ctu_plan *p)
     TileSet *all[] = { &p->t_tc, &p->t_sweep[0], &p->t_sweep[1], &p->t_sweep[2] };
     // a previous step may still read the tables being replaced
     HIP_TRY(hipDeviceSynchronize());
+    if ((st = upload_into(p->hboxes, p->dboxes, p->hboxes.size())) != CTU_OK) return st;
     for (TileSet *ts : all)
         if ((st = upload_into(ts->h, ts->d, ts->cap)) != CTU_OK) return st;
     return CTU_OK;
