@@ -207,13 +207,6 @@ __global__ __launch_bounds__(NT) void k_havg(const HBox *fbox, const HTile *tile
     if (missing) atomicAdd(missing, 1);
 }
 
-// fails_acc[q] += fails[q]
-__global__ void k_add_fails(int *acc, const int *f)
-{
-    const int t = threadIdx.x;
-    if (t < 5) acc[t] += f[t];
-}
-
 // Leaf mask of one level (one byte per ghosted cell, the state layout / 9):
 // 1 on interior cells that no box of the next finer level covers (the
 // cells of Sec. 4.2 whose source time step counts), 0 elsewhere.  fbox is

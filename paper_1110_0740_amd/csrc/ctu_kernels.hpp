@@ -1,8 +1,8 @@
 // ctu_kernels.hpp -- HIP kernels of the CTU-GLM step (Sec. 3.1) for gfx950.
 //
 // One step of a batch of ghosted boxes is a short chain of launches:
-//   k_reset      zero the rate / dpp / failure outputs (graph-safe, no memset)
-//   k_cons2prim  V = V(U) on every ghosted cell                       (a1)
+//   k_cons2prim  V = V(U) on every ghosted cell; clears the rate and dpp
+//                outputs (graph-safe, no memset)                      (a1)
 //   k_shock_hll, k_shock_mm
 //                App. B zone flags (shock-adaptive runs only)
 //   k_pdiv       parabolic runs: the parabolic fluxes Pi^n of V^n on
@@ -194,14 +194,37 @@ template <int Z = 0> __global__ void k_reset(double *rate, double *dpp, int *fai
     if (t >= 2 && t < 2 + 5 && fails) fails[t - 2] = 0;
 }
 
+// The failure counters of a step.  The primitive recovery counts into the
+// plan's own counters, which are zero between steps; the t^n kernel's first
+// block moves them into the caller's (added to them if `acc`) and clears them,
+// so that no launch of its own zeroes the caller's counters.
+struct FailCounts {
+    int *plan, *out;
+    int acc;
+};
+
+__device__ __forceinline__ void move_fails(const FailCounts &f)
+{
+    if (f.out && blockIdx.x == 0 && threadIdx.x < 5) {
+        const int q = threadIdx.x;
+        f.out[q] = (f.acc ? f.out[q] : 0) + f.plan[q];
+        f.plan[q] = 0;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // elementwise maps: tile = (box, first cell); one cell per thread
 // ---------------------------------------------------------------------------
 
 template <int PHYS, typename R>
 __global__ __launch_bounds__(NT) void k_cons2prim(const KBox *boxes, const KTile *tiles, const R *U, R *V,
-                                                  int *fails, R gam, int out_ws)
+                                                  int *fails, R gam, int out_ws, double *rate, double *dpp)
 {
+    // in a step: the first block clears the maxima that the sweeps raise
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0 && rate) *rate = 0.0;
+        if (threadIdx.x == 1 && dpp) *dpp = 0.0;
+    }
     KTile tl = tiles[blockIdx.x];
     const KBox &bx = boxes[tl.box];
     long long c = tl.a + threadIdx.x;
@@ -818,6 +841,7 @@ template <typename R> struct TArgs {
     const double *params;
     KOpts o;
     int lm;           // planes per chunk along the marching axis (>= 1)
+    FailCounts cnt;
 };
 
 // the nine primitive variables of cell c
@@ -883,6 +907,7 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
     __shared__ R Gx[NV][GXS];
     __shared__ R Gy[(DIM == 3) ? NV : 1][GYS];
 
+    move_fails(a.cnt);
     const int tid = threadIdx.x;
     // lane in the wave that solves the extra faces; consecutive blocks go to
     // the eight XCDs in turn, so the choice mixes in the block's place within
@@ -1198,6 +1223,7 @@ template <typename R> struct MtArgs {
     R *T[3];              // transverse increments (workspace)
     const double *params;
     KOpts o;
+    FailCounts cnt;       // k_mtT only
 };
 
 // normal predictor (the sweep's) of the cell at c along D
@@ -1294,6 +1320,7 @@ __global__ __launch_bounds__(NT) void k_mtflux(MtArgs<R> a)
 template <int DIM, typename R>
 __global__ __launch_bounds__(NT) void k_mtT(MtArgs<R> a)
 {
+    move_fails(a.cnt);
     const KTile tl = a.tiles[blockIdx.x];
     const KBox bx = a.boxes[tl.box];
     const int c = tl.a + (int)threadIdx.x;

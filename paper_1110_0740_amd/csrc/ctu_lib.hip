@@ -148,6 +148,7 @@ struct ctu_plan {
     // graph
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
+    int *dcnt = nullptr;  // the primitive recovery's failure counters, zero between steps
     hipEvent_t tune_ev[2] = { nullptr, nullptr };  // autotuner timing events
     // per-stage event timing
     bool timing = false;
@@ -172,7 +173,7 @@ void free_plan(ctu_plan *p)
     if (p->graph) (void)hipGraphDestroy(p->graph);
     void *ptrs[] = { p->dboxes, p->dregs, p->drface, p->t_cells.d, p->t_tc.d, p->t_sweep[0].d, p->t_sweep[1].d,
                      p->t_sweep[2].d, p->t_cfl.d, p->ws_block, p->drefl, p->dcell_start, p->t_mt[0].d, p->t_mt[1].d,
-                     p->t_mt[2].d, p->t_pf.d, p->t_pd.d };
+                     p->t_mt[2].d, p->t_pf.d, p->t_pd.d, p->dcnt };
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     delete p;
@@ -700,18 +701,17 @@ template <typename R> hipError_t launch_pflux(ctu_plan *p, const R *V, int div, 
 
 template <typename R>
 ctu_status enqueue_step(ctu_plan *p, const void *U_in, void *U_out, const double *params, const void *L0, double *reg,
-                        double *rate, double *dpp, int32_t *fails, hipStream_t s)
+                        double *rate, double *dpp, int32_t *fails, hipStream_t s, int acc = 0)
 {
     const int dim = p->opts.dim;
     const bool par = p->opts.parabolic_mask != 0;
-    hipLaunchKernelGGL(k_reset<0>, dim3(1), dim3(64), 0, s, rate, dpp, (int *)fails);
-    HIP_TRY(hipGetLastError());
+    const FailCounts cnt{ fails ? p->dcnt : nullptr, (int *)fails, acc };
     const R gam = (R)p->opts.gamma;
     {
         StageTimer tm(p, 0, s);
         HIP_TRY(with_phys(p->combo.phys, [&](auto P) {
             hipLaunchKernelGGL((k_cons2prim<decltype(P)::value, R>), dim3(p->t_cells.n()), dim3(NT), 0, s,
-                               p->dboxes, p->t_cells.d, (const R *)U_in, (R *)p->wsV, (int *)fails, gam, 1);
+                               p->dboxes, p->t_cells.d, (const R *)U_in, (R *)p->wsV, cnt.plan, gam, 1, rate, dpp);
             return hipGetLastError();
         }));
         if (p->wsFlag) {
@@ -737,6 +737,7 @@ ctu_status enqueue_step(ctu_plan *p, const void *U_in, void *U_out, const double
         }
         ma.params = params;
         ma.o = p->ko;
+        ma.cnt = cnt;
         for (int D = 0; D < dim; D++) {
             hipError_t e;
             ma.tiles = p->t_mt[D].d;
@@ -768,6 +769,7 @@ ctu_status enqueue_step(ctu_plan *p, const void *U_in, void *U_out, const double
         ta.params = params;
         ta.o = p->ko;
         ta.lm = p->split.lm;
+        ta.cnt = cnt;
         hipError_t e;
         if constexpr (sizeof(R) == 4)
             e = launch_tcouple_f32(dim, par ? 1 : 0, p->combo, p->t_tc.n(), ta, s);
@@ -1092,6 +1094,10 @@ static ctu_status create_plan(int32_t dev, uint32_t flags, const ctu_opts *opts,
         free_plan(p);
         return st;
     }
+    if ((st = upload(std::vector<int>(8, 0), &p->dcnt)) != CTU_OK) {
+        free_plan(p);
+        return st;
+    }
     if (hipEventCreate(&p->tune_ev[0]) != hipSuccess || hipEventCreate(&p->tune_ev[1]) != hipSuccess) {
         free_plan(p);
         return fail(CTU_ERR_HIP, "hipEventCreate failed");
@@ -1278,9 +1284,10 @@ ctu_status ctu_tune_cache_clear(void)
     return CTU_OK;
 }
 
-ctu_status ctu_step(ctu_plan *plan, const void *U_in_dev, void *U_out_dev, const double *params_dev,
-                    const void *cool_L0_dev, double *reg_dev, double *rate_dev, double *dpp_dev, int32_t *fails_dev,
-                    void *stream)
+// ctu_step; acc != 0 adds the failure counts to fails_dev instead of setting it
+static ctu_status step_plan(ctu_plan *plan, const void *U_in_dev, void *U_out_dev, const double *params_dev,
+                            const void *cool_L0_dev, double *reg_dev, double *rate_dev, double *dpp_dev,
+                            int32_t *fails_dev, void *stream, int acc)
 {
     ctu_status st = check_step_args(plan, U_in_dev, U_out_dev, params_dev, cool_L0_dev, reg_dev, rate_dev);
     if (st != CTU_OK) return st;
@@ -1289,10 +1296,19 @@ ctu_status ctu_step(ctu_plan *plan, const void *U_in_dev, void *U_out_dev, const
     hipStream_t s = (hipStream_t)stream;
     if (plan->esize == 4)
         return enqueue_step<float>(plan, U_in_dev, U_out_dev, params_dev, cool_L0_dev, reg_dev, rate_dev, dpp_dev,
-                                   fails_dev, s);
+                                   fails_dev, s, acc);
     return enqueue_step<double>(plan, U_in_dev, U_out_dev, params_dev, cool_L0_dev, reg_dev, rate_dev, dpp_dev,
-                                fails_dev, s);
+                                fails_dev, s, acc);
 }
+
+ctu_status ctu_step(ctu_plan *plan, const void *U_in_dev, void *U_out_dev, const double *params_dev,
+                    const void *cool_L0_dev, double *reg_dev, double *rate_dev, double *dpp_dev, int32_t *fails_dev,
+                    void *stream)
+{
+    return step_plan(plan, U_in_dev, U_out_dev, params_dev, cool_L0_dev, reg_dev, rate_dev, dpp_dev, fails_dev, stream,
+                     0);
+}
+
 
 ctu_status ctu_step_graph_capture(ctu_plan *plan, const void *U_in_dev, void *U_out_dev, const double *params_dev,
                                   const void *cool_L0_dev, double *reg_dev, double *rate_dev, double *dpp_dev,
@@ -1427,10 +1443,12 @@ ctu_status ctu_cons_to_prim(ctu_plan *plan, const void *U_dev, void *V_dev, int3
         constexpr int PH = decltype(P)::value;
         if (plan->esize == 4)
             hipLaunchKernelGGL((k_cons2prim<PH, float>), dim3(nb), dim3(NT), 0, s, plan->dboxes, plan->t_cells.d,
-                               (const float *)U_dev, (float *)V_dev, (int *)fails_dev, (float)plan->opts.gamma, 0);
+                               (const float *)U_dev, (float *)V_dev, (int *)fails_dev, (float)plan->opts.gamma, 0, (double *)nullptr,
+                               (double *)nullptr);
         else
             hipLaunchKernelGGL((k_cons2prim<PH, double>), dim3(nb), dim3(NT), 0, s, plan->dboxes, plan->t_cells.d,
-                               (const double *)U_dev, (double *)V_dev, (int *)fails_dev, plan->opts.gamma, 0);
+                               (const double *)U_dev, (double *)V_dev, (int *)fails_dev, plan->opts.gamma, 0, (double *)nullptr,
+                               (double *)nullptr);
         return hipGetLastError();
     }));
     return CTU_OK;
@@ -1695,7 +1713,6 @@ struct ctu_hier {
     int dev = 0;  // the device current at creation: tables, counters and launches
     int esize = 8, base = 0, nlev = 0, ng = 0;
     std::vector<HierLevel> lev;
-    int *dfails = nullptr;  // per-step failure counts inside the cycle
 };
 
 namespace {
@@ -1711,7 +1728,6 @@ void free_hier(ctu_hier *h)
         for (void *q : ptrs)
             if (q) (void)hipFree(q);
     }
-    if (h->dfails) (void)hipFree(h->dfails);
     delete h;
 }
 
@@ -1915,13 +1931,9 @@ ctu_status advance_level(const CycleArgs &c, int lev, const void *pold, const vo
     void *out = c.cur[lev] ? c.Ua[lev] : c.Ub[lev];
     ctu_status st = hier_fill_any(h, lev, in, pold, pnew, alpha, c.missing, c.s);
     if (st != CTU_OK) return st;
-    st = ctu_step(c.plans[lev], in, out, c.params[lev], c.L0 ? c.L0[lev] : nullptr, c.reg, c.rate + lev,
-                  c.dpp ? c.dpp + lev : nullptr, h->dfails, c.s);
+    st = step_plan(c.plans[lev], in, out, c.params[lev], c.L0 ? c.L0[lev] : nullptr, c.reg, c.rate + lev,
+                   c.dpp ? c.dpp + lev : nullptr, c.fails, c.s, 1);
     if (st != CTU_OK) return st;
-    if (c.fails) {
-        hipLaunchKernelGGL(k_add_fails, dim3(1), dim3(64), 0, c.s, (int *)c.fails, (const int *)h->dfails);
-        HIP_TRY(hipGetLastError());
-    }
     c.cur[lev] ^= 1;
     if (lev + 1 < h->nlev) {
         for (int q = 0; q < 2; q++)
@@ -2086,10 +2098,6 @@ ctu_status ctu_hier_create(int32_t precision, int32_t base, int32_t nlev, const 
             free_hier(h);
             return st;
         }
-    }
-    if (hipMalloc((void **)&h->dfails, 8 * sizeof(int)) != hipSuccess) {
-        free_hier(h);
-        return fail(CTU_ERR_NOMEM, "hipMalloc of the cycle counters failed");
     }
     *out = h;
     return CTU_OK;
