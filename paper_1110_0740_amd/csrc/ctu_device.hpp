@@ -172,16 +172,16 @@ template <int D, typename R> __device__ __forceinline__ void flux_mhd(const R *V
 // gas enthalpy w(rho, p)
 template <bool TM, typename R> __device__ __forceinline__ R rmhd_w(R rho, R p, R gam)
 {
-    if constexpr (TM) return R(2.5) * p + sqrt(R(2.25) * p * p + rho * rho);
-    else return rho + gam * p / (gam - R(1));
+    if constexpr (TM) return R(2.5) * p + root(R(2.25) * p * p + rho * rho);
+    else return rho + quot(gam * p, gam - R(1));
 }
 
 // sound speed squared, (dp/drho)_s rho / w along the adiabat de = (w/rho)
 // drho of e = w - p: Gamma p / w, or p (5w - 8p) / (3 w (w - p)) for TM
 template <bool TM, typename R> __device__ __forceinline__ R rmhd_cs2(R p, R w, R gam)
 {
-    if constexpr (TM) return p * (R(5) * w - R(8) * p) / (R(3) * w * (w - p));
-    else return gam * p / w;
+    if constexpr (TM) return quot(p * (R(5) * w - R(8) * p), R(3) * w * (w - p));
+    else return quot(gam * p, w);
 }
 
 template <bool TM, typename R> __device__ __forceinline__ void p2c_rmhd(const R *V, R *U, R gam)
@@ -189,8 +189,8 @@ template <bool TM, typename R> __device__ __forceinline__ void p2c_rmhd(const R 
     R v2 = sq(V[MX1]) + sq(V[MX2]) + sq(V[MX3]);
     R B2 = sq(V[BX1]) + sq(V[BX2]) + sq(V[BX3]);
     R vB = V[MX1] * V[BX1] + V[MX2] * V[BX2] + V[MX3] * V[BX3];
-    R lor2 = R(1) / (R(1) - v2);
-    R lor = sqrt(lor2);
+    R lor2 = rcp(R(1) - v2);
+    R lor = root(lor2);
     R w = rmhd_w<TM>(V[RHO], V[PRS], gam);
     R wl2 = w * lor2;
     U[RHO] = V[RHO] * lor;
@@ -228,9 +228,9 @@ __device__ __forceinline__ int c2p_rmhd(const double *U, double *V, double gam, 
     // 4p^2 - 5wp + w^2 - rho^2 = 0 with w - 5p/2 >= 0
     auto pres = [&](double rho, double w, double &dpdw, double &dpdr) {
         if constexpr (TM) {
-            const double s = sqrt(9.0 * w * w + 16.0 * rho * rho);
-            dpdw = 0.125 * (5.0 - 9.0 * w / s);
-            dpdr = -2.0 * rho / s;
+            const double s2 = 9.0 * w * w + 16.0 * rho * rho, is = rsq(s2), s = s2 * is;
+            dpdw = 0.125 * (5.0 - 9.0 * w * is);
+            dpdr = -2.0 * rho * is;
             return 0.125 * (5.0 * w - s);
         } else {
             dpdw = gfac;
@@ -251,9 +251,8 @@ __device__ __forceinline__ int c2p_rmhd(const double *U, double *V, double gam, 
     bool conv = false;
     double v2 = 0.0;
     for (int it = 0; it < 60; ++it) {
-        double sw = S / W;
-        double WB = W + B2;
-        double iWB = 1.0 / WB;
+        const double iW = rcp(W), sw = S * iW;
+        const double iWB = rcp(W + B2);
         v2 = (m2 + sw * sw * (2.0 * W + B2)) * iWB * iWB;
         double f, df;
         if (!(v2 < 1.0)) {
@@ -262,17 +261,17 @@ __device__ __forceinline__ int c2p_rmhd(const double *U, double *V, double gam, 
             f = -1.0;
             df = 0.0;
         } else {
-            double sq1 = sqrt(1.0 - v2);
+            const double lor = rsq(1.0 - v2), sq1 = (1.0 - v2) * lor;
             double dpdw, dpdr;
             double p = pres(D * sq1, W * (1.0 - v2), dpdw, dpdr);
             f = W - p + 0.5 * B2 + 0.5 * (v2 * B2 - sw * sw) - D - E;
-            double dv2 = -2.0 * sw * sw / (W * WB) - 2.0 * v2 * iWB;
+            double dv2 = -2.0 * sw * sw * iW * iWB - 2.0 * v2 * iWB;
             // w = W (1 - v^2), rho = D sqrt(1 - v^2)
-            double dp = dpdw * ((1.0 - v2) - W * dv2) + dpdr * (-0.5 * D * dv2 / sq1);
-            df = 1.0 - dp + 0.5 * B2 * dv2 + sw * sw / W;
+            double dp = dpdw * ((1.0 - v2) - W * dv2) + dpdr * (-0.5 * D * dv2 * lor);
+            df = 1.0 - dp + 0.5 * B2 * dv2 + sw * sw * iW;
             if (f > 0.0) hi = W; else lo = W;
         }
-        double Wn = (df > 0.0) ? W - f / df : 0.5 * (lo + hi);
+        double Wn = (df > 0.0) ? W - f * rcp(df) : 0.5 * (lo + hi);
         // a Newton step within the tolerance has converged wherever it lands:
         // at the root the step rounds onto the bracket end just moved to W,
         // and falling back to bisection there would walk away from the root
@@ -282,15 +281,13 @@ __device__ __forceinline__ int c2p_rmhd(const double *U, double *V, double gam, 
         if (fabs(Wn - W) <= tol * fmax(W, wscale)) { W = Wn; conv = true; break; }
         W = Wn;
     }
-    double sw = S / W;
-    v2 = (m2 + sw * sw * (2.0 * W + B2)) / ((W + B2) * (W + B2));
-    double sq1 = sqrt(1.0 - v2);
-    V[RHO] = D * sq1;
+    const double sw = S * rcp(W), iWB = rcp(W + B2);
+    v2 = (m2 + sw * sw * (2.0 * W + B2)) * iWB * iWB;
+    V[RHO] = D * root(1.0 - v2);
     {
         double dpdw, dpdr;
         V[PRS] = pres(V[RHO], W * (1.0 - v2), dpdw, dpdr);
     }
-    double iWB = 1.0 / (W + B2);
     V[MX1] = (U[MX1] + sw * U[BX1]) * iWB;
     V[MX2] = (U[MX2] + sw * U[BX2]) * iWB;
     V[MX3] = (U[MX3] + sw * U[BX3]) * iWB;
@@ -308,7 +305,7 @@ template <int D, bool TM, typename R> __device__ __forceinline__ void flux_rmhd(
     R v2 = sq(V[MX1]) + sq(V[MX2]) + sq(V[MX3]);
     R B2 = sq(V[BX1]) + sq(V[BX2]) + sq(V[BX3]);
     R vB = V[MX1] * V[BX1] + V[MX2] * V[BX2] + V[MX3] * V[BX3];
-    R wl2 = rmhd_w<TM>(V[RHO], V[PRS], gam) / (R(1) - v2);
+    R wl2 = quot(rmhd_w<TM>(V[RHO], V[PRS], gam), R(1) - v2);
     // E = -v x B; E_n E_c terms and |E|^2 = v^2 B^2 - (v.B)^2
     R E0 = V[MX3] * V[BX2] - V[MX2] * V[BX3];
     R E1 = V[MX1] * V[BX3] - V[MX3] * V[BX1];
@@ -338,15 +335,15 @@ __device__ __forceinline__ void speeds_rmhd(const R *V, R gam, R &lmin, R &lmax,
     R w = rmhd_w<TM>(V[RHO], V[PRS], gam);
     R cs2 = rmhd_cs2<TM>(V[PRS], w, gam);
     R bb2 = B2 * (R(1) - v2) + vB * vB;
-    R ca2 = bb2 / (w + bb2);
+    R ca2 = quot(bb2, w + bb2);
     R a2 = cs2 + ca2 - cs2 * ca2;
     R vn = V[MX1 + D];
-    R den = R(1) / (R(1) - v2 * a2);
+    R den = rcp(R(1) - v2 * a2);
     R disc = (R(1) - v2) * (R(1) - v2 * a2 - vn * vn * (R(1) - a2));
     disc = disc > R(0) ? disc : R(0);
-    R root = sqrt(a2 * disc);
-    lmin = (vn * (R(1) - a2) - root) * den;
-    lmax = (vn * (R(1) - a2) + root) * den;
+    R rt = root(a2 * disc);
+    lmin = (vn * (R(1) - a2) - rt) * den;
+    lmax = (vn * (R(1) - a2) + rt) * den;
     if (!xs) return;
     // exact fast speeds: the outermost roots of the lab-frame dispersion
     // quartic g = w (1 - cs^2) A^4 - (w cs^2 + b^2) A^2 (1 - l^2)
@@ -400,7 +397,7 @@ template <int PHYS, typename R> __device__ __forceinline__ double w_guess(const 
     } else {
         const double v2 = sq((double)V[MX1]) + sq((double)V[MX2]) + sq((double)V[MX3]);
         const double w = rmhd_w<PHYS == PHYS_RMHD_TM>((double)V[RHO], (double)V[PRS], (double)gam);
-        return (v2 < 1.0) ? w / (1.0 - v2) : 0.0;
+        return (v2 < 1.0) ? w * rcp(1.0 - v2) : 0.0;
     }
 }
 
