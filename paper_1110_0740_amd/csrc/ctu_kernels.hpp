@@ -197,7 +197,8 @@ template <int Z = 0> __global__ void k_reset(double *rate, double *dpp, int *fai
 // The failure counters of a step.  The primitive recovery counts into the
 // plan's own counters, which are zero between steps; the t^n kernel's first
 // block moves them into the caller's (added to them if `acc`) and clears them,
-// so that no launch of its own zeroes the caller's counters.
+// so that no launch of its own zeroes the caller's counters.  Kernels do this
+// last: a store ahead of the table loads would make them vector loads.
 struct FailCounts {
     int *plan, *out;
     int acc;
@@ -220,23 +221,24 @@ template <int PHYS, typename R>
 __global__ __launch_bounds__(NT) void k_cons2prim(const KBox *boxes, const KTile *tiles, const R *U, R *V,
                                                   int *fails, R gam, int out_ws, double *rate, double *dpp)
 {
+    KTile tl = tiles[blockIdx.x];
+    const KBox &bx = boxes[tl.box];
+    long long c = tl.a + threadIdx.x;
+    if (c < bx.cells) {
+        R u[NV], v[NV];
+#pragma unroll
+        for (int q = 0; q < NV; q++) u[q] = U[bx.uoff + q * bx.cells + c];
+        int f = c2p<PHYS>(u, v, gam);
+        count_fails(f, fails);
+        long long o = out_ws ? bx.woff : bx.uoff;
+#pragma unroll
+        for (int q = 0; q < NV; q++) V[o + q * bx.cells + c] = v[q];
+    }
     // in a step: the first block clears the maxima that the sweeps raise
     if (blockIdx.x == 0) {
         if (threadIdx.x == 0 && rate) *rate = 0.0;
         if (threadIdx.x == 1 && dpp) *dpp = 0.0;
     }
-    KTile tl = tiles[blockIdx.x];
-    const KBox &bx = boxes[tl.box];
-    long long c = tl.a + threadIdx.x;
-    if (c >= bx.cells) return;
-    R u[NV], v[NV];
-#pragma unroll
-    for (int q = 0; q < NV; q++) u[q] = U[bx.uoff + q * bx.cells + c];
-    int f = c2p<PHYS>(u, v, gam);
-    count_fails(f, fails);
-    long long o = out_ws ? bx.woff : bx.uoff;
-#pragma unroll
-    for (int q = 0; q < NV; q++) V[o + q * bx.cells + c] = v[q];
 }
 
 template <int PHYS, typename R>
@@ -907,7 +909,6 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
     __shared__ R Gx[NV][GXS];
     __shared__ R Gy[(DIM == 3) ? NV : 1][GYS];
 
-    move_fails(a.cnt);
     const int tid = threadIdx.x;
     // lane in the wave that solves the extra faces; consecutive blocks go to
     // the eight XCDs in turn, so the choice mixes in the block's place within
@@ -1132,8 +1133,13 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
 #pragma unroll
                     for (int q = 0; q < NKT; q++) keep(Tk[q]);
                 }
+                // (the flag made opaque: two copies of the whole loop, one per
+                // kind of store, measured slower)
+                int tnt = bx.tnt;
+                asm volatile("" : "+v"(tnt));
+                tnt = __builtin_amdgcn_readfirstlane(tnt);
                 auto store_t = [&](int q, R t0, R t1, R t2) {
-                    if (bx.tnt) {
+                    if (tnt) {
                         bT0.template st<2>(q, ct, t0);
                         bT1.template st<2>(q, ct, t1);
                         if constexpr (DIM == 3) bT2.template st<2>(q, ct, t2);
@@ -1200,6 +1206,7 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
         }
         __syncthreads();
     }
+    move_fails(a.cnt);
 }
 
 // ---------------------------------------------------------------------------
@@ -1318,9 +1325,8 @@ __global__ __launch_bounds__(NT) void k_mtflux(MtArgs<R> a)
 }
 
 template <int DIM, typename R>
-__global__ __launch_bounds__(NT) void k_mtT(MtArgs<R> a)
+__device__ __forceinline__ void mt_increments(const MtArgs<R> &a)
 {
-    move_fails(a.cnt);
     const KTile tl = a.tiles[blockIdx.x];
     const KBox bx = a.boxes[tl.box];
     const int c = tl.a + (int)threadIdx.x;
@@ -1369,6 +1375,13 @@ __global__ __launch_bounds__(NT) void k_mtT(MtArgs<R> a)
             bT.st(q, ct, t);
         }
     }
+}
+
+template <int DIM, typename R>
+__global__ __launch_bounds__(NT) void k_mtT(MtArgs<R> a)
+{
+    mt_increments<DIM>(a);
+    move_fails(a.cnt);
 }
 
 // ---------------------------------------------------------------------------

@@ -242,7 +242,7 @@ bool use_flat(const ctu_plan *p, const KBox &bx)
 // chip and leave a shorter tail.  SplitCost estimates a launch's time, in
 // units of one round's cost on a compute unit that holds `res` blocks (the
 // register-bound residence): whole batches of 256 * res blocks cost res
-// units per round; the blocks left over run fewer to a compute unit, where a
+// units per round and kStart rounds to start; the blocks left over run fewer to a compute unit, where a
 // round takes kConc units (one block alone is bound by the latency of its
 // ~1500 dependent instructions) plus kPro rounds to start.  Against measured
 // sweeps (64^3 .. 256^3, 131 x 97 x 75, FP32 and FP64, 1 .. 8 runs per line)
@@ -264,10 +264,11 @@ struct SplitCost {
     }
     double time(int res) const
     {
-        constexpr double kConc[4] = { 0.0, 1.6, 2.4, 3.0 }, kPro = 0.6;
+        constexpr double kConc[4] = { 0.0, 1.6, 2.4, 3.0 }, kPro = 0.6, kStart = 0.5;
         const long long slots = (long long)kCus * res, full = blocks / slots, rem = blocks % slots;
         const double avg = work / (double)blocks;
-        double t = (double)full * avg * res;
+        // every block starts up; the batches together take at least the longest block
+        double t = full > 0 ? std::max((double)full * (avg + kStart), longest + kPro) * res : 0.0;
         if (rem > 0) {
             const int conc = (int)((rem + kCus - 1) / kCus);
             t += (longest + kPro) * (conc >= res ? (double)res : kConc[conc]);
