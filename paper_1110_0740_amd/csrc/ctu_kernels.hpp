@@ -346,14 +346,6 @@ __global__ __launch_bounds__(NT) void k_shock_mm(const KBox *boxes, const KTile 
     if (mm) fb[c] |= FLAG_MINMOD;
 }
 
-// A vector store reads its data registers after issue, and the compiler
-// waits for the store to complete before an instruction overwrites them.
-// Values stored from short-lived temporaries make the next instructions that
-// reuse those registers wait for the stores; keep(v) marks the registers of
-// stored values as still in use at a later point (the next store of the same
-// values), so that no other value takes them in between.
-template <typename R> __device__ __forceinline__ void keep(const R &v) { asm volatile("" ::"v"(v)); }
-
 // ---------------------------------------------------------------------------
 // Parabolic face fluxes (Sec. 2.1.1, Sec. 3.1, App. A).
 //
@@ -883,20 +875,20 @@ __device__ __forceinline__ void tface_s(const R *VL_in, const R *VR_in, int cL, 
     }
 }
 
-#ifndef CTU_TC_WAVES_PAR_F32
-#define CTU_TC_WAVES_PAR_F32 1
-#endif
-// the FP64 parabolic kernel at two waves (12 bytes of spills, without the
-// U^n / P prefetch) runs 15 % faster than at one wave with it
+// the FP64 parabolic kernel at two waves (12 bytes of spills) runs 15 %
+// faster than at one
 #ifndef CTU_TC_WAVES_PAR_F64
 #define CTU_TC_WAVES_PAR_F64 2
 #endif
-// the FP32 fixed-option HLLD kernel needs 174 registers by itself; three waves
-// leave 168
+// the FP32 HLLD kernels need a few registers more than the 168 that three
+// waves leave (174 without parabolic terms).  The parabolic one ran at two
+// waves with U^n and P loaded a plane ahead and its stored values held in
+// registers of their own; at three waves without either, 160^3 takes
+// @@ us instead of 374
 template <int PAR, int RS, int VAR, typename R> constexpr int tc_waves()
 {
-    if (!PAR && sizeof(R) == 4 && VAR == VAR_FAST && RS == RS_HLLD) return 3;
-    return PAR ? (sizeof(R) == 4 ? CTU_TC_WAVES_PAR_F32 : CTU_TC_WAVES_PAR_F64) : 1;
+    if (sizeof(R) == 4 && (PAR || VAR == VAR_FAST) && RS == RS_HLLD) return 3;
+    return (PAR && sizeof(R) == 8) ? CTU_TC_WAVES_PAR_F64 : 1;
 }
 
 template <int DIM, int PHYS, int RS, int PAR, int VAR, typename R>
@@ -1017,33 +1009,8 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
     R Vc[NV], Vp[NV];
     if (inplane) ld_cell(bV, cb + (m0 - 1) * sM, Vp);
     R Gm_prev[NV], Lx_prev[NV], Ly_prev[NV];
-    // the stored T_d and V^{n+1/2} values of the last finished cell, held
-    // until the next cell's stores (see keep): FP32 parabolic runs, whose
-    // two waves per SIMD leave the registers (6 % faster there; in the
-    // three-wave kernels the extra registers cost a wave)
-    constexpr bool KEEPT = PAR && sizeof(R) == 4;
-    // FP32 parabolic runs load U^n and P of the cell to finish ahead of the
-    // plane's face solves; FP64 loads them where they are used (the held
-    // registers would cost its second wave per SIMD)
-    constexpr bool PRE = PAR && sizeof(R) == 4;
-    constexpr int NKT = KEEPT ? (DIM + (PAR ? 1 : 0)) * NV : 1;
-    R Tk[NKT];
-#pragma unroll
-    for (int q = 0; q < NKT; q++) Tk[q] = R(0);
     for (int m = m0; m <= m1 + 1; m++) {
         const int c = cb + m * sM, ec = eb + m * sM;  // this plane's cells
-        // U^n and P of the cell this plane finishes, loaded ahead of the face
-        // solves that hide their latency (PRE)
-        R Upre[NV], Ppre[7];
-        if constexpr (PRE) {
-            if (inplane && m > m0) {
-                const int pc = c - sM;
-#pragma unroll
-                for (int q = 0; q < NV; q++) Upre[q] = Blk<R>(a.U + bx.uoff, bx.cells).ld(q, pc);
-#pragma unroll
-                for (int q = 0; q < 7; q++) Ppre[q] = Pf[q * cs + pc];
-            }
-        }
         // in FP32 every state this plane's faces read is loaded together, so
         // that one wait covers the three loads; in FP64 the two neighbour
         // states are loaded at their faces (held across the marching face
@@ -1123,16 +1090,12 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
                     Pd[RHO] = R(0);
                     Pd[PSI] = R(0);
 #pragma unroll
-                    for (int q = 0; q < 7; q++) Pd[MX1 + q] = PRE ? Ppre[q] : (inplane ? Pf[q * cs + pc] : R(0));
+                    for (int q = 0; q < 7; q++) Pd[MX1 + q] = inplane ? Pf[q * cs + pc] : R(0);
                 }
                 auto addp = [&](R x, int q) -> R {
                     if constexpr (PAR) return x + Pd[q];
                     else return x;
                 };
-                if constexpr (KEEPT) {
-#pragma unroll
-                    for (int q = 0; q < NKT; q++) keep(Tk[q]);
-                }
                 // (the flag made opaque: two copies of the whole loop, one per
                 // kind of store, measured slower)
                 int tnt = bx.tnt;
@@ -1164,28 +1127,15 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
                         t1 = addp(Lx_prev[q], q);
                         S[q] = addp(Lx_prev[q] + Lm[q], q);
                     }
-                    if constexpr (KEEPT) {
-                        Tk[q] = t0;
-                        Tk[NV + q] = t1;
-                        if constexpr (DIM == 3) Tk[2 * NV + q] = t2;
-                    } else {
-                        store_t(q, t0, t1, t2);
-                    }
-                }
-                if constexpr (KEEPT) {
-                    // after the loop: its arithmetic stays one basic block
-#pragma unroll
-                    for (int q = 0; q < NV; q++)
-                        store_t(q, Tk[q], Tk[NV + q], Tk[(DIM == 3 ? 2 * NV : 0) + q]);
+                    store_t(q, t0, t1, t2);
                 }
                 if constexpr (PAR) {
                     R u[NV], v[NV];
 #pragma unroll
-                    for (int q = 0; q < NV; q++) u[q] = (PRE ? Upre[q] : Blk<R>(a.U + bx.uoff, bx.cells).ld(q, pc)) + hdt * S[q];
+                    for (int q = 0; q < NV; q++) u[q] = Blk<R>(a.U + bx.uoff, bx.cells).ld(q, pc) + hdt * S[q];
                     c2p<PHYS_MHD>(u, v, gam);
 #pragma unroll
                     for (int q = 0; q < NV; q++) {
-                        if constexpr (KEEPT) Tk[DIM * NV + q] = v[q];
                         if (inplane) Blk<R>(a.Vh + bx.woff, bx.cells).st(q, pc, v[q]);
                     }
                 }
