@@ -884,7 +884,7 @@ __device__ __forceinline__ void tface_s(const R *VL_in, const R *VR_in, int cL, 
 // waves leave (174 without parabolic terms).  The parabolic one ran at two
 // waves with U^n and P loaded a plane ahead and its stored values held in
 // registers of their own; at three waves without either, 160^3 takes
-// @@ us instead of 374
+// 353 us instead of 374
 template <int PAR, int RS, int VAR, typename R> constexpr int tc_waves()
 {
     if (sizeof(R) == 4 && (PAR || VAR == VAR_FAST) && RS == RS_HLLD) return 3;
