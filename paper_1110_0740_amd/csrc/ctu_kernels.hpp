@@ -366,6 +366,12 @@ __global__ __launch_bounds__(NT) void k_shock_mm(const KBox *boxes, const KTile 
 // A block owns TX x TY in-plane cells (3D: x, y; 2D: x) and marches along
 // the last axis over a chunk of planes, with three planes of the eight
 // staged fields (rho, v, B, T = p / rho) and a one-cell in-plane halo in LDS.
+// Both were bound by their instructions, a third of them addresses and the
+// divisions by dx; with whole-vector LDS reads at constant offsets (PVec),
+// 1/dx in scalar registers (PGrad, the same FP32 rounding) and planes loaded
+// one plane ahead (PStage) k_pdiv went from 202 to 136 us at 160^3 FP32
+// (1026 -> 730 vector instructions), and from 40 to 31 us (k_pflux from 32 to
+// 24) on 70 x 57 x 45 FP64, where a division took ten instructions.
 // ---------------------------------------------------------------------------
 
 constexpr int NPF = 8;  // slots per face
@@ -404,58 +410,119 @@ __device__ __forceinline__ R pf_energy(R E, R Fn, R Fm, const KOpts &o, R pL, R 
     if (o.parab & PB_TC) {
         if (o.phi > 0.0 && Fm > R(0)) {
             R pu = (Fn < R(0)) ? pL : pR;
-            R q = R(5.0 * o.phi) * pu * sqrt(pu) / sqrt(R(0.5) * (rL + rR));
-            Fn = q / (Fm + q) * Fn;
+            R q = quot(R(5.0 * o.phi) * pu * root(pu), root(R(0.5) * (rL + rR)));
+            Fn = quot(q, Fm + q) * Fn;
         }
         E += Fn;
     }
     return E;
 }
 
-// slots of the D-face below the lane's cell from the three staged planes
-// (P[0], P[1], P[2] = planes m-1, m, m+1, field f at f * HP); l is the
-// lane's in-plane slot
+// The eight staged fields of a cell as 16-byte vectors, (rho, v) | (B, T) in
+// FP32 and pairs in FP64, vector g of slot h at (g * HP + h) * VW: a face
+// reads ten cells, and whole vectors take a quarter (half) of the LDS
+// instructions and addresses of single fields, at consecutive slots without
+// bank conflicts.
+template <typename R> struct PVec {
+    static constexpr int VW = 16 / (int)sizeof(R), NG = 8 / VW;
+    typedef R V __attribute__((ext_vector_type(16 / sizeof(R))));
+};
+
+// a product that is rounded by itself, as the quotient in its place would be
+template <typename R> __device__ __forceinline__ R mul_rn(R a, R b)
+{
+#pragma clang fp contract(off)
+    return a * b;
+}
+
+// 1 / dx and 1 / (4 dx) per axis, in scalar registers
+template <typename R> struct PGrad {
+    R d1[3], d4[3];
+
+    __device__ __forceinline__ explicit PGrad(const KBox &bx)
+    {
+#pragma unroll
+        for (int e = 0; e < 3; e++) {
+            d1[e] = uni(R(1) / R(bx.dx[e]));
+            d4[e] = uni(R(1) / (R(4) * R(bx.dx[e])));
+        }
+    }
+    static __device__ __forceinline__ float uni(float x)
+    {
+        return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+    }
+    static __device__ __forceinline__ double uni(double x)
+    {
+        const uint64_t u = __builtin_bit_cast(uint64_t, x);
+        const uint32_t l = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u),
+                       h = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+        return __builtin_bit_cast(double, (uint64_t)h << 32 | l);
+    }
+};
+
+// slots of the D-face below the lane's cell; P[0], P[1], P[2] point into the
+// staged planes m-1, m, m+1 at the slot one below the lane's in each in-plane
+// direction, so that every offset is a non-negative constant
 template <int DIM, int D, typename R>
-__device__ __forceinline__ void pflux_face(const R *const *P, int l, const KBox &bx, const KOpts &o, R *out)
+__device__ __forceinline__ void pflux_face(const R *const *P, const PGrad<R> &dg, const KOpts &o, R *out)
 {
     constexpr int n = Ax<D>::n, t = Ax<D>::t, b = Ax<D>::b;
     constexpr int HP = PTile<DIM>::HP, HX = PTile<DIM>::HX;
+    using PV = PVec<R>;
+    using V = typename PV::V;
+    constexpr int L0 = (DIM == 3) ? HX + 1 : 1;
     // plane and in-plane offsets of the unit step along axis e
     auto dm_of = [](int e) { return e == DIM - 1 ? 1 : 0; };
     auto dl_of = [](int e) { return e == DIM - 1 ? 0 : (e == 0 ? 1 : HX); };
-    // field f of the cell at (dm, dl) from the lane's cell
-    auto val = [&](int f, int dm, int dl) -> R { return P[1 + dm][f * HP + l + dl]; };
+    // four fields of the cell at (dm, dl) from the lane's cell: half 0 is
+    // (rho, v), half 1 (B, T)
+    struct F4 {
+        R f[4];
+    };
+    auto cell = [&](int half, int dm, int dl) {
+        F4 r;
+#pragma unroll
+        for (int g = 0; g < PV::NG / 2; g++) {
+            const V v = *(const V *)(P[1 + dm] + ((half * (PV::NG / 2) + g) * HP + L0 + dl) * PV::VW);
+#pragma unroll
+            for (int k = 0; k < PV::VW; k++) r.f[g * PV::VW + k] = v[k];
+        }
+        return r;
+    };
     const int aM = -dm_of(D), aL = -dl_of(D);  // cell A
-    const R rA = val(0, aM, aL), rB = val(0, 0, 0);
-    const R irs = R(1) / (rA + rB);
-    const R rhof = R(0.5) * (rA + rB);
-    R vf[3], Bf[3];
-#pragma unroll
-    for (int c = 0; c < 3; c++) {
-        vf[c] = (rA * val(1 + c, aM, aL) + rB * val(1 + c, 0, 0)) * irs;
-        Bf[c] = R(0.5) * (val(4 + c, aM, aL) + val(4 + c, 0, 0));
-    }
-    // gradients of (v_x, v_y, v_z, B_x, B_y, B_z, T) at the face
-    R g[7][3];
-#pragma unroll
-    for (int f = 0; f < 7; f++) {
-        g[f][D] = (val(1 + f, 0, 0) - val(1 + f, aM, aL)) / R(bx.dx[D]);
+    // gradient along e of the four fields of a half, A and B its two cells
+    auto grad = [&](int half, const F4 &A, const F4 &B, R (*g)[3]) {
 #pragma unroll
         for (int e = 0; e < 3; e++) {
-            if (e == D) continue;
-            if (e >= DIM) {
-                g[f][e] = R(0);
-                continue;
+            if (e == D) {
+#pragma unroll
+                for (int f = 0; f < 4; f++) g[f][e] = mul_rn(B.f[f] - A.f[f], dg.d1[e]);
+            } else if (e >= DIM) {
+#pragma unroll
+                for (int f = 0; f < 4; f++) g[f][e] = R(0);
+            } else {
+                const int em = dm_of(e), el = dl_of(e);
+                const F4 u0 = cell(half, em, el), u1 = cell(half, aM + em, aL + el);
+                const F4 d0 = cell(half, -em, -el), d1 = cell(half, aM - em, aL - el);
+#pragma unroll
+                for (int f = 0; f < 4; f++) {
+                    const R up = u0.f[f] + u1.f[f], dn = d0.f[f] + d1.f[f];
+                    g[f][e] = mul_rn(up - dn, dg.d4[e]);
+                }
             }
-            const int em = dm_of(e), el = dl_of(e);
-            R up = val(1 + f, em, el) + val(1 + f, aM + em, aL + el);
-            R dn = val(1 + f, -em, -el) + val(1 + f, aM - em, aL - el);
-            g[f][e] = (up - dn) / (R(4) * R(bx.dx[e]));
         }
-    }
+    };
 #pragma unroll
     for (int q = 0; q < NPF; q++) out[q] = R(0);
     if (o.parab & PB_VISC) {
+        const F4 A = cell(0, aM, aL), B = cell(0, 0, 0);
+        R g4[4][3];
+        grad(0, A, B, g4);
+        const R(*g)[3] = g4 + 1;  // of v
+        const R rA = A.f[0], rB = B.f[0], irs = rcp(rA + rB), rhof = R(0.5) * (rA + rB);
+        R vf[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) vf[c] = (rA * A.f[1 + c] + rB * B.f[1 + c]) * irs;
         R divv = g[0][0] + g[1][1] + g[2][2];
         R mu = rhof * R(o.nu);
         R tau[3];
@@ -466,61 +533,99 @@ __device__ __forceinline__ void pflux_face(const R *const *P, int l, const KBox 
         }
         out[PF_E] += vf[0] * tau[0] + vf[1] * tau[1] + vf[2] * tau[2];
     }
-    if (o.parab & PB_RES) {
-        R J[3];
-        J[0] = g[5][1] - g[4][2];
-        J[1] = g[3][2] - g[5][0];
-        J[2] = g[4][0] - g[3][1];
-        R eta = R(o.eta);
-        out[PF_BT] = eta * J[b];
-        out[PF_BB] = -(eta * J[t]);
-        out[PF_E] -= eta * (J[t] * Bf[b] - J[b] * Bf[t]);
-    }
-    if (o.parab & PB_TC) {
-        R B2 = Bf[0] * Bf[0] + Bf[1] * Bf[1] + Bf[2] * Bf[2];
-        R bh[3] = { R(0), R(0), R(0) };
-        if (B2 > R(0)) {
-            R ib = R(1) / sqrt(B2);
+    if (o.parab & (PB_RES | PB_TC)) {
+        const F4 A = cell(1, aM, aL), B = cell(1, 0, 0);
+        R g[4][3];  // of B and T
+        grad(1, A, B, g);
+        R Bf[3];
 #pragma unroll
-            for (int c = 0; c < 3; c++) bh[c] = Bf[c] * ib;
+        for (int c = 0; c < 3; c++) Bf[c] = R(0.5) * (A.f[c] + B.f[c]);
+        if (o.parab & PB_RES) {
+            R J[3];
+            J[0] = g[2][1] - g[1][2];
+            J[1] = g[0][2] - g[2][0];
+            J[2] = g[1][0] - g[0][1];
+            R eta = R(o.eta);
+            out[PF_BT] = eta * J[b];
+            out[PF_BB] = -(eta * J[t]);
+            out[PF_E] -= eta * (J[t] * Bf[b] - J[b] * Bf[t]);
         }
-        R bg = bh[0] * g[6][0] + bh[1] * g[6][1] + bh[2] * g[6][2];
-        R Fc[3];
+        if (o.parab & PB_TC) {
+            R B2 = Bf[0] * Bf[0] + Bf[1] * Bf[1] + Bf[2] * Bf[2];
+            R bh[3] = { R(0), R(0), R(0) };
+            if (B2 > R(0)) {
+                R ib = R(1) / root(B2);
 #pragma unroll
-        for (int c = 0; c < 3; c++) Fc[c] = R(o.kpar) * bh[c] * bg + R(o.kperp) * (g[6][c] - bh[c] * bg);
-        out[PF_FN] = Fc[n];
-        out[PF_FM] = sqrt(Fc[0] * Fc[0] + Fc[1] * Fc[1] + Fc[2] * Fc[2]);
+                for (int c = 0; c < 3; c++) bh[c] = Bf[c] * ib;
+            }
+            R bg = bh[0] * g[3][0] + bh[1] * g[3][1] + bh[2] * g[3][2];
+            R Fc[3];
+#pragma unroll
+            for (int c = 0; c < 3; c++) Fc[c] = R(o.kpar) * bh[c] * bg + R(o.kperp) * (g[3][c] - bh[c] * bg);
+            out[PF_FN] = Fc[n];
+            out[PF_FM] = root(Fc[0] * Fc[0] + Fc[1] * Fc[1] + Fc[2] * Fc[2]);
+        }
     }
 }
 
-// stage plane m of V (rho, v, B, T = p / rho) over the tile's cells and a
-// one-cell in-plane halo into S (field f at f * HP), cells of the load range
-// [lo, hi] only
-template <int DIM, typename R>
-__device__ __forceinline__ void pf_stage(R *S, const R *Vb, const KBox &bx, const int *lo, const int *hi, int x0,
-                                         int y0, int m)
-{
+// Stages planes of V (rho, v, B, T = p / rho) over the tile's cells and a
+// one-cell in-plane halo, cells of the load range [lo, hi] only: each lane
+// holds at most two slots, whose places are found once, and a plane is loaded
+// (load) one plane of work before it is written to LDS (put)
+template <int DIM, typename R> struct PStage {
     using PT = PTile<DIM>;
-    constexpr int AM = DIM - 1;
-    if (m < lo[AM] || m > hi[AM]) return;
-    const int cs = (int)bx.cells;
-    for (int h = threadIdx.x; h < PT::HP; h += NT) {
-        const int hx = h % PT::HX, hy = h / PT::HX;
-        const int xx = x0 - 1 + hx, yy = y0 - 1 + hy;
-        if (xx < lo[0] || xx > hi[0]) continue;
-        if (DIM == 3 && (yy < lo[1] || yy > hi[1])) continue;
-        const int c = (DIM == 3) ? cidx(bx, xx, yy, m) : cidx(bx, xx, m, 0);
-        const R rho = Vb[RHO * cs + c];
-        R *d = S + h;
-        d[0] = rho;
+    using PV = PVec<R>;
+    static constexpr int NS = (PT::HP + NT - 1) / NT;
+    static constexpr int SIZE = 8 * PT::HP;  // values per staged plane
+    Blk<R> V;
+    int e[NS], sM, lo, hi;
+    bool ok[NS];
+    R r[NS][8];
+
+    __device__ __forceinline__ PStage(const R *Vb, const KBox &bx, const int *l, const int *h, int x0, int y0)
+        : V(Vb, bx.cells), sM((DIM == 3) ? bx.N[0] * bx.N[1] : bx.N[0]), lo(l[DIM - 1]), hi(h[DIM - 1])
+    {
 #pragma unroll
-        for (int q = 0; q < 3; q++) {
-            d[(1 + q) * PT::HP] = Vb[(MX1 + q) * cs + c];
-            d[(4 + q) * PT::HP] = Vb[(BX1 + q) * cs + c];
+        for (int k = 0; k < NS; k++) {
+            const int s = threadIdx.x + k * NT, xx = x0 - 1 + s % PT::HX, yy = y0 - 1 + s / PT::HX;
+            ok[k] = s < PT::HP && xx >= l[0] && xx <= h[0] && (DIM == 2 || (yy >= l[1] && yy <= h[1]));
+            e[k] = (DIM == 3) ? yy * bx.N[0] + xx : xx;
         }
-        d[7 * PT::HP] = Vb[PRS * cs + c] / rho;
     }
-}
+    __device__ __forceinline__ void load(int m)
+    {
+        if (m < lo || m > hi) return;
+#pragma unroll
+        for (int k = 0; k < NS; k++)
+            if (ok[k]) {
+                const int c = e[k] + m * sM;
+                r[k][0] = V.ld(RHO, c);
+#pragma unroll
+                for (int q = 0; q < 3; q++) {
+                    r[k][1 + q] = V.ld(MX1 + q, c);
+                    r[k][4 + q] = V.ld(BX1 + q, c);
+                }
+                r[k][7] = V.ld(PRS, c);
+            }
+    }
+    // the plane loaded last (m as given there) into S
+    __device__ __forceinline__ void put(R *S, int m)
+    {
+        if (m < lo || m > hi) return;
+#pragma unroll
+        for (int k = 0; k < NS; k++)
+            if (ok[k]) {
+                r[k][7] = quot(r[k][7], r[k][0]);
+#pragma unroll
+                for (int g = 0; g < PV::NG; g++) {
+                    typename PV::V v;
+#pragma unroll
+                    for (int j = 0; j < PV::VW; j++) v[j] = r[k][g * PV::VW + j];
+                    *(typename PV::V *)(S + (g * PT::HP + threadIdx.x + k * NT) * PV::VW) = v;
+                }
+            }
+    }
+};
 
 // Pi^{n+1/2} face slots of the sweeps (all eight, conduction unsaturated):
 // faces below cells g .. g+n along D at positions g .. g+n-1 across it,
@@ -530,7 +635,7 @@ __global__ __launch_bounds__(NT) void k_pflux(PArgs<R> a)
 {
     using PT = PTile<DIM>;
     constexpr int AM = DIM - 1;  // marching axis
-    __shared__ R S[3][8 * PT::HP];
+    __shared__ __align__(16) R S[3][8 * PT::HP];
     const int tid = threadIdx.x;
     const KTile tl = a.tiles[blockIdx.x];
     const KBox bx = a.boxes[tl.box];
@@ -548,7 +653,8 @@ __global__ __launch_bounds__(NT) void k_pflux(PArgs<R> a)
     const int x0 = lo[0] + 1 + tl.a, y0 = (DIM == 3) ? lo[1] + 1 + tl.b : 0;
     const int tx = tid % PT::TX, ty = tid / PT::TX;
     const int x = x0 + tx, y = y0 + ty;
-    const int l = (DIM == 3) ? (ty + 1) * PT::HX + tx + 1 : tx + 1;
+    // the lane's lowest staged neighbour (see pflux_face)
+    const int l0 = ((DIM == 3) ? ty * PT::HX + tx : tx) * PVec<R>::VW;
     // the faces of this lane's position (per plane, the marching bounds below)
     const bool inx = x <= hi[0] - 1, iny = DIM == 2 || y <= hi[1] - 1;
     const bool fx = x <= hi[0] && iny;
@@ -557,21 +663,27 @@ __global__ __launch_bounds__(NT) void k_pflux(PArgs<R> a)
     const int m0 = lo[AM] + 1 + tl.c, m1 = min(m0 + a.lm - 1, hi[AM]);
 
     int r0 = 0, r1 = 1, r2 = 2;  // ring slots of planes m-1, m, m+1
-    pf_stage<DIM>(&S[r0][0], Vb, bx, lo, hi, x0, y0, m0 - 1);
-    pf_stage<DIM>(&S[r1][0], Vb, bx, lo, hi, x0, y0, m0);
+    const PGrad<R> dg(bx);
+    PStage<DIM, R> st(Vb, bx, lo, hi, x0, y0);
+    st.load(m0 - 1);
+    st.put(&S[r0][0], m0 - 1);
+    st.load(m0);
+    st.put(&S[r1][0], m0);
+    st.load(m0 + 1);
     for (int m = m0; m <= m1; m++) {
-        pf_stage<DIM>(&S[r2][0], Vb, bx, lo, hi, x0, y0, m + 1);
+        st.put(&S[r2][0], m + 1);
+        if (m < m1) st.load(m + 2);
         __syncthreads();
-        const R *P[3] = { &S[r0][0], &S[r1][0], &S[r2][0] };
+        const R *P[3] = { &S[r0][0] + l0, &S[r1][0] + l0, &S[r2][0] + l0 };
         const int c = (DIM == 3) ? cidx(bx, x, y, m) : cidx(bx, x, m, 0);
         R out[NPF];
         const bool inm = m <= hi[AM] - 1;  // the in-plane faces' marching bound
         auto face = [&](auto Dc) {
             constexpr int D = decltype(Dc)::value;
-            pflux_face<DIM, D>(P, l, bx, o, out);
-            R *dst = Pb + D * NPF * cs + c;
+            pflux_face<DIM, D>(P, dg, o, out);
+            const Blk<R> dst(Pb + D * NPF * cs, bx.cells);
 #pragma unroll
-            for (int q = 0; q < NPF; q++) dst[q * cs] = out[q];
+            for (int q = 0; q < NPF; q++) dst.st(q, c, out[q]);
         };
         if (fx && inm) face(std::integral_constant<int, 0>());
         if constexpr (DIM == 3)
@@ -613,7 +725,7 @@ __global__ __launch_bounds__(NT) void k_pdiv(PArgs<R> a)
     constexpr int AM = DIM - 1;
     constexpr int NS = PF_E + 1;  // saturated slots
     static_assert(DIM == 2 || (PT::TX <= 64 && 64 % PT::TX == 0), "a tile row must lie within one wave");
-    __shared__ R S[3][8 * PT::HP];
+    __shared__ __align__(16) R S[3][8 * PT::HP];
     __shared__ R Fy[(DIM == 3) ? NS : 1][(DIM == 3) ? NT : 1];
     __shared__ R Fx2[(DIM == 2) ? NS : 1][(DIM == 2) ? NT : 1];
     const int tid = threadIdx.x;
@@ -632,7 +744,8 @@ __global__ __launch_bounds__(NT) void k_pdiv(PArgs<R> a)
     const int x0 = lo[0] + 1 + tl.a, y0 = (DIM == 3) ? lo[1] + 1 + tl.b : 0;
     const int tx = tid % PT::TX, ty = tid / PT::TX;
     const int x = x0 + tx, y = y0 + ty;
-    const int l = (DIM == 3) ? (ty + 1) * PT::HX + tx + 1 : tx + 1;
+    // the lane's lowest staged neighbour (see pflux_face)
+    const int l0 = ((DIM == 3) ? ty * PT::HX + tx : tx) * PVec<R>::VW;
     const bool iny = DIM == 2 || y <= hi[1] - 1;
     const bool fx = x <= hi[0] && iny;
     const bool fy = DIM == 3 && x <= hi[0] - 1 && y <= hi[1];
@@ -643,26 +756,44 @@ __global__ __launch_bounds__(NT) void k_pdiv(PArgs<R> a)
     const R ix = R(1.0 / bx.dx[0]), iy = R(1.0 / bx.dx[1]), iz = R(1.0 / bx.dx[2]);
 
     int r0 = 0, r1 = 1, r2 = 2;  // ring slots of planes m-1, m, m+1
-    pf_stage<DIM>(&S[r0][0], Vb, bx, lo, hi, x0, y0, m0 - 1);
-    pf_stage<DIM>(&S[r1][0], Vb, bx, lo, hi, x0, y0, m0);
+    const PGrad<R> dg(bx);
+    PStage<DIM, R> st(Vb, bx, lo, hi, x0, y0);
+    st.load(m0 - 1);
+    st.put(&S[r0][0], m0 - 1);
+    st.load(m0);
+    st.put(&S[r1][0], m0);
+    st.load(m0 + 1);
+    const Blk<R> bV(Vb, bx.cells), bP(Pb, bx.cells);
+    const bool sat = (o.parab & PB_TC) && o.phi > 0.0;
+    // pressure of the cell below the lane's marching face
+    R pm = R(0);
+    if (sat && fm) pm = bV.ld(PRS, (DIM == 3) ? cidx(bx, x, y, m0 - 1) : cidx(bx, x, m0 - 1, 0));
     R Fm_prev[NS], Pin[NV], Fx[NS];
 #pragma unroll
     for (int q = 0; q < NS; q++) Fx[q] = R(0);
     for (int m = m0; m <= m1 + 1; m++) {
-        pf_stage<DIM>(&S[r2][0], Vb, bx, lo, hi, x0, y0, m + 1);
+        st.put(&S[r2][0], m + 1);
+        if (m < m1 + 1) st.load(m + 2);
         __syncthreads();
-        const R *P[3] = { &S[r0][0], &S[r1][0], &S[r2][0] };
+        const R *P[3] = { &S[r0][0] + l0, &S[r1][0] + l0, &S[r2][0] + l0 };
         const int c = (DIM == 3) ? cidx(bx, x, y, m) : cidx(bx, x, m, 0);
         R out[NPF];
+        // the pressures of the lane's cell and of the cells below its faces
+        // (the marching one carried), loaded ahead of the face arithmetic
+        R pc = R(0), px = R(0), py = R(0);
+        if (sat && (fx || fy || fm)) {
+            pc = bV.ld(PRS, c);
+            px = bV.ld(PRS, c - 1);
+            if constexpr (DIM == 3) py = bV.ld(PRS, c - bx.N[0]);
+        }
         // the D-face below the lane's cell, saturated with the states of its
         // two cells
         auto face = [&](auto Dc) {
             constexpr int D = decltype(Dc)::value;
-            pflux_face<DIM, D>(P, l, bx, o, out);
-            const int sD = (D == 0) ? 1 : (D == 1 ? bx.N[0] : bx.N[0] * bx.N[1]);
-            const R rA = P[(D == AM) ? 0 : 1][l - ((D == AM) ? 0 : (D == 0 ? 1 : PT::HX))];
-            const R rB = P[1][l];
-            out[PF_E] = pf_energy(out[PF_E], out[PF_FN], out[PF_FM], o, Vb[PRS * cs + c - sD], Vb[PRS * cs + c], rA, rB);
+            pflux_face<DIM, D>(P, dg, o, out);
+            constexpr int L0 = (DIM == 3) ? PT::HX + 1 : 1, dA = (D == AM) ? 0 : (D == 0 ? 1 : PT::HX);
+            const R rA = P[(D == AM) ? 0 : 1][(L0 - dA) * PVec<R>::VW], rB = P[1][L0 * PVec<R>::VW];
+            out[PF_E] = pf_energy(out[PF_E], out[PF_FN], out[PF_FM], o, (D == AM) ? pm : (D == 0 ? px : py), pc, rA, rB);
         };
         if (m <= m1) {
             if (fx) {
@@ -703,7 +834,7 @@ __global__ __launch_bounds__(NT) void k_pdiv(PArgs<R> a)
                 for (int q = 0; q < NV; q++) Pc[q] = Pin[q];
                 pdiv_add<AM>(Fm_prev, Fm, (DIM == 3) ? iz : iy, Pc);
 #pragma unroll
-                for (int q = 0; q < 7; q++) Pb[q * cs + c - sM] = Pc[MX1 + q];
+                for (int q = 0; q < 7; q++) bP.st(q, c - sM, Pc[MX1 + q]);
             }
             // in-plane part of this plane's cell
             if (m <= m1) {
@@ -727,6 +858,7 @@ __global__ __launch_bounds__(NT) void k_pdiv(PArgs<R> a)
 #pragma unroll
             for (int q = 0; q < NS; q++) Fm_prev[q] = Fm[q];
         }
+        pm = pc;
         const int rt = r0;
         r0 = r1;
         r1 = r2;
@@ -734,21 +866,20 @@ __global__ __launch_bounds__(NT) void k_pdiv(PArgs<R> a)
     }
 }
 
-// Pi on the D-face below cell c from its slots (Pf: the box's slots), the
+// Pi on the D-face below cell c from its slots (f: the box's slots of D), the
 // saturated conduction flux upwinded with the face states (pL, rL), (pR, rR)
 template <int D, typename R>
-__device__ __forceinline__ void parab_face(const R *Pf, int cs, int c, const KOpts &o, R pL, R pR, R rL, R rR, R *Pi)
+__device__ __forceinline__ void parab_face(const Blk<R> &f, int c, const KOpts &o, R pL, R pR, R rL, R rR, R *Pi)
 {
     constexpr int t = Ax<D>::t, b = Ax<D>::b;
-    const R *f = Pf + D * NPF * cs + c;
 #pragma unroll
     for (int q = 0; q < NV; q++) Pi[q] = R(0);
 #pragma unroll
-    for (int q = 0; q < 3; q++) Pi[MX1 + q] = f[(PF_M + q) * cs];
-    Pi[BX1 + t] = f[PF_BT * cs];
-    Pi[BX1 + b] = f[PF_BB * cs];
+    for (int q = 0; q < 3; q++) Pi[MX1 + q] = f.ld(PF_M + q, c);
+    Pi[BX1 + t] = f.ld(PF_BT, c);
+    Pi[BX1 + b] = f.ld(PF_BB, c);
     const bool tc = (o.parab & PB_TC) != 0;
-    Pi[ENG] = pf_energy(f[PF_E * cs], tc ? f[PF_FN * cs] : R(0), tc ? f[PF_FM * cs] : R(0), o, pL, pR, rL, rR);
+    Pi[ENG] = pf_energy(f.ld(PF_E, c), tc ? f.ld(PF_FN, c) : R(0), tc ? f.ld(PF_FM, c) : R(0), o, pL, pR, rL, rR);
 }
 
 
@@ -914,7 +1045,7 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
     const R hdt = R(0.5 * box_dt(bx, a.params));
     const int cs = (int)bx.cells;
     const R *Vb = a.V + bx.woff;
-    const R *Pf = PAR ? a.PF + (bx.woff / NV) * (NPF * DIM) : nullptr;
+    const Blk<R> bPf(PAR ? a.PF + (bx.woff / NV) * (NPF * DIM) : a.V, bx.cells);
     const Blk<R> bV(Vb, bx.cells);
     const unsigned char *fb = SHK ? a.flag + bx.woff / NV : nullptr;
     const Blk<R> bT0(a.T[0] + bx.toff, bx.tcells), bT1(a.T[1] + bx.toff, bx.tcells);
@@ -1090,7 +1221,7 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
                     Pd[RHO] = R(0);
                     Pd[PSI] = R(0);
 #pragma unroll
-                    for (int q = 0; q < 7; q++) Pd[MX1 + q] = inplane ? Pf[q * cs + pc] : R(0);
+                    for (int q = 0; q < 7; q++) Pd[MX1 + q] = inplane ? bPf.ld(q, pc) : R(0);
                 }
                 auto addp = [&](R x, int q) -> R {
                     if constexpr (PAR) return x + Pd[q];
@@ -1597,7 +1728,8 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
             }
             if (o.parab) {
                 R Pi[NV];
-                parab_face<D>(a.PF + (bx.woff / NV) * (NPF * dim), cs, c, o, pL, pR, rL, rR, Pi);
+                parab_face<D>(Blk<R>(a.PF + (bx.woff / NV) * (NPF * dim) + D * NPF * bx.cells, bx.cells), c, o, pL, pR,
+                              rL, rR, Pi);
 #pragma unroll
                 for (int q = 0; q < NV; q++) F[q] -= Pi[q];
             }
