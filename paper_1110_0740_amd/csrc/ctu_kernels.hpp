@@ -66,11 +66,16 @@ struct KBox {
     long long toff;
     int tcells, tp, tpl, tF, tS, tHp;
     int tnt;  // rows are whole lines: the t^n kernel stores them nontemporally
+    // layout of the parabolic face slots (see pidx): NPF planes of pcells
+    // elements per direction from element poff of the field
+    long long poff;
+    int pcells, pp, pS, pHp;
+    int pnt;  // rows are whole lines (1), stored nontemporally (2)
 };
 
-// T_d fields live on the region [g-1, g+n] only (positions rx, ry, rz from its
-// low corner) in an order of their own, in which every row of a t^n tile is
-// whole 128-byte lines that one block writes: row pitch tp and plane pitch tpl
+// T_d fields, and V^{n+1/2} of parabolic runs, live on the region [g-1, g+n]
+// only (positions rx, ry, rz from its low corner) in an order of their own, in
+// which every row of a t^n tile is whole 128-byte lines that one block writes: row pitch tp and plane pitch tpl
 // are padded to lines, the columns from tF on (strip tiles) are stored
 // transposed, ry fastest with pitch tHp, from tS; boxes on the flat t^n layout
 // keep its position order (tp = n[0] + 3).  The padding is written too.  Rows
@@ -85,6 +90,19 @@ __device__ __forceinline__ int tidx(const KBox &bx, int rx, int ry, int rz)
 {
     const int main = rz * bx.tpl + ry * bx.tp + rx, strip = bx.tS + (2 * rz + rx - bx.tF) * bx.tHp + ry;
     return rx < bx.tF ? main : strip;
+}
+
+// the same for the parabolic slots of the D-faces at positions fx, fy, fz from
+// the low corner of the box (0 .. n along D, 0 .. n-1 across): rows of the n
+// faces that k_pflux's tiles own, pitch pp in whole lines; the x faces at
+// fx = n[0] are a plane of their own from pS, fy fastest with pitch pHp.  At
+// 160^3 FP32 k_pflux took 186 us with the ghosted row pitch and 130 with this
+// layout, and the x sweep after it 265 and 214.  Every layout fits the ghosted
+// extent; where padded rows would not, rows keep the box's width.
+template <int D> __device__ __forceinline__ int pidx(const KBox &bx, int fx, int fy, int fz)
+{
+    const int main = (fz * (bx.n[1] + (D == 1)) + fy) * bx.pp + fx;
+    return (D == 0 && fx == bx.n[0]) ? bx.pS + fz * bx.pHp + fy : main;
 }
 
 // the step of a box: the plan's dt, halved per level of a multi-level plan
@@ -571,25 +589,33 @@ __device__ __forceinline__ void pflux_face(const R *const *P, const PGrad<R> &dg
 // Stages planes of V (rho, v, B, T = p / rho) over the tile's cells and a
 // one-cell in-plane halo, cells of the load range [lo, hi] only: each lane
 // holds at most two slots, whose places are found once, and a plane is loaded
-// (load) one plane of work before it is written to LDS (put)
-template <int DIM, typename R> struct PStage {
+// (load) one plane of work before it is written to LDS (put).  TL: the source
+// is V^{n+1/2}, in the T_d layout, otherwise V^n
+template <int DIM, bool TL, typename R> struct PStage {
     using PT = PTile<DIM>;
     using PV = PVec<R>;
     static constexpr int NS = (PT::HP + NT - 1) / NT;
     static constexpr int SIZE = 8 * PT::HP;  // values per staged plane
     Blk<R> V;
-    int e[NS], sM, lo, hi;
+    int e[NS], sM[NS], lo, hi;
     bool ok[NS];
     R r[NS][8];
 
     __device__ __forceinline__ PStage(const R *Vb, const KBox &bx, const int *l, const int *h, int x0, int y0)
-        : V(Vb, bx.cells), sM((DIM == 3) ? bx.N[0] * bx.N[1] : bx.N[0]), lo(l[DIM - 1]), hi(h[DIM - 1])
+        : V(Vb, TL ? bx.tcells : bx.cells), lo(l[DIM - 1]), hi(h[DIM - 1])
     {
 #pragma unroll
         for (int k = 0; k < NS; k++) {
             const int s = threadIdx.x + k * NT, xx = x0 - 1 + s % PT::HX, yy = y0 - 1 + s / PT::HX;
             ok[k] = s < PT::HP && xx >= l[0] && xx <= h[0] && (DIM == 2 || (yy >= l[1] && yy <= h[1]));
-            e[k] = (DIM == 3) ? yy * bx.N[0] + xx : xx;
+            if constexpr (TL) {
+                const int rx = xx - bx.g[0] + 1, ry = (DIM == 3) ? yy - bx.g[1] + 1 : 0;
+                sM[k] = (DIM == 2) ? bx.tp : (rx >= bx.tF ? 2 * bx.tHp : bx.tpl);
+                e[k] = tidx(bx, rx, ry, 0) - (bx.g[DIM - 1] - 1) * sM[k];
+            } else {
+                sM[k] = (DIM == 3) ? bx.N[0] * bx.N[1] : bx.N[0];
+                e[k] = (DIM == 3) ? yy * bx.N[0] + xx : xx;
+            }
         }
     }
     __device__ __forceinline__ void load(int m)
@@ -598,7 +624,7 @@ template <int DIM, typename R> struct PStage {
 #pragma unroll
         for (int k = 0; k < NS; k++)
             if (ok[k]) {
-                const int c = e[k] + m * sM;
+                const int c = e[k] + m * sM[k];
                 r[k][0] = V.ld(RHO, c);
 #pragma unroll
                 for (int q = 0; q < 3; q++) {
@@ -640,9 +666,8 @@ __global__ __launch_bounds__(NT) void k_pflux(PArgs<R> a)
     const KTile tl = a.tiles[blockIdx.x];
     const KBox bx = a.boxes[tl.box];
     const KOpts &o = a.o;
-    const int cs = (int)bx.cells;
-    const R *Vb = a.V + bx.woff;
-    R *Pb = a.PF + (bx.woff / NV) * (NPF * DIM);
+    const R *Vb = a.V + bx.toff;
+    R *Pb = a.PF + bx.poff;
     // load range [lo, hi] per axis (x, y, marching in 3D; x, marching in 2D)
     int lo[3] = { 0, 0, 0 }, hi[3] = { 0, 0, 0 };
 #pragma unroll
@@ -664,7 +689,7 @@ __global__ __launch_bounds__(NT) void k_pflux(PArgs<R> a)
 
     int r0 = 0, r1 = 1, r2 = 2;  // ring slots of planes m-1, m, m+1
     const PGrad<R> dg(bx);
-    PStage<DIM, R> st(Vb, bx, lo, hi, x0, y0);
+    PStage<DIM, true, R> st(Vb, bx, lo, hi, x0, y0);
     st.load(m0 - 1);
     st.put(&S[r0][0], m0 - 1);
     st.load(m0);
@@ -675,20 +700,40 @@ __global__ __launch_bounds__(NT) void k_pflux(PArgs<R> a)
         if (m < m1) st.load(m + 2);
         __syncthreads();
         const R *P[3] = { &S[r0][0] + l0, &S[r1][0] + l0, &S[r2][0] + l0 };
-        const int c = (DIM == 3) ? cidx(bx, x, y, m) : cidx(bx, x, m, 0);
         R out[NPF];
         const bool inm = m <= hi[AM] - 1;  // the in-plane faces' marching bound
-        auto face = [&](auto Dc) {
+        // D-face slots, solved where `real` and stored by the lanes of the
+        // row's lines: those past the row's last face fill its padding
+        auto face = [&](auto Dc, bool real) {
             constexpr int D = decltype(Dc)::value;
-            pflux_face<DIM, D>(P, dg, o, out);
-            const Blk<R> dst(Pb + D * NPF * cs, bx.cells);
+            if (real) pflux_face<DIM, D>(P, dg, o, out);
+            const Blk<R> dst(Pb + (long long)(D * NPF) * bx.pcells, bx.pcells);
+            const int fx = x - bx.g[0], fy = (DIM == 3 ? y : m) - bx.g[1], fz = (DIM == 3) ? m - bx.g[2] : 0;
+            if (fx < bx.pp && (real || bx.pnt)) {
+                // (the x face past a row without padding goes to its own plane)
+                const int pi = (fz * (bx.n[1] + (D == 1)) + fy) * bx.pp + fx;
+                int pnt = bx.pnt;
+                asm volatile("" : "+v"(pnt));
+                if (__builtin_amdgcn_readfirstlane(pnt) == 2) {
 #pragma unroll
-            for (int q = 0; q < NPF; q++) dst.st(q, c, out[q]);
+                    for (int q = 0; q < NPF; q++) dst.template st<2>(q, pi, out[q]);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < NPF; q++) dst.st(q, pi, out[q]);
+                }
+            }
+            if (D == 0 && real && fx == bx.n[0]) {
+                const int pi = pidx<D>(bx, fx, fy, fz);
+#pragma unroll
+                for (int q = 0; q < NPF; q++) dst.st(q, pi, out[q]);
+            }
         };
-        if (fx && inm) face(std::integral_constant<int, 0>());
+#pragma unroll
+        for (int q = 0; q < NPF; q++) out[q] = R(0);
+        if (inm && iny) face(std::integral_constant<int, 0>(), fx);
         if constexpr (DIM == 3)
-            if (fy && inm) face(std::integral_constant<int, 1>());
-        if (fm) face(std::integral_constant<int, AM>());
+            if (inm && y <= hi[1]) face(std::integral_constant<int, 1>(), fy);
+        if (iny) face(std::integral_constant<int, AM>(), fm);
         __syncthreads();
         const int rt = r0;
         r0 = r1;
@@ -757,7 +802,7 @@ __global__ __launch_bounds__(NT) void k_pdiv(PArgs<R> a)
 
     int r0 = 0, r1 = 1, r2 = 2;  // ring slots of planes m-1, m, m+1
     const PGrad<R> dg(bx);
-    PStage<DIM, R> st(Vb, bx, lo, hi, x0, y0);
+    PStage<DIM, false, R> st(Vb, bx, lo, hi, x0, y0);
     st.load(m0 - 1);
     st.put(&S[r0][0], m0 - 1);
     st.load(m0);
@@ -866,7 +911,7 @@ __global__ __launch_bounds__(NT) void k_pdiv(PArgs<R> a)
     }
 }
 
-// Pi on the D-face below cell c from its slots (f: the box's slots of D), the
+// Pi on the D-face at index c of its slots (f: the box's slots of D), the
 // saturated conduction flux upwinded with the face states (pL, rL), (pR, rR)
 template <int D, typename R>
 __device__ __forceinline__ void parab_face(const Blk<R> &f, int c, const KOpts &o, R pL, R pR, R rL, R rR, R *Pi)
@@ -1049,7 +1094,7 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
     const Blk<R> bV(Vb, bx.cells);
     const unsigned char *fb = SHK ? a.flag + bx.woff / NV : nullptr;
     const Blk<R> bT0(a.T[0] + bx.toff, bx.tcells), bT1(a.T[1] + bx.toff, bx.tcells);
-    const Blk<R> bT2(DIM == 3 ? a.T[2] + bx.toff : Vb, bx.tcells);
+    const Blk<R> bT2(DIM == 3 ? a.T[2] + bx.toff : Vb, bx.tcells), bVh(PAR ? a.Vh + bx.toff : Vb, bx.tcells);
     const R ix = R(1.0 / bx.dx[0]), iy = R(1.0 / bx.dx[1]), iz = R(1.0 / bx.dx[2]);
     const int hi0 = bx.g[0] + bx.n[0];                       // last region cell along x
     const int hi1 = (DIM == 3) ? bx.g[1] + bx.n[1] : 0;
@@ -1266,9 +1311,7 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
                     for (int q = 0; q < NV; q++) u[q] = Blk<R>(a.U + bx.uoff, bx.cells).ld(q, pc) + hdt * S[q];
                     c2p<PHYS_MHD>(u, v, gam);
 #pragma unroll
-                    for (int q = 0; q < NV; q++) {
-                        if (inplane) Blk<R>(a.Vh + bx.woff, bx.cells).st(q, pc, v[q]);
-                    }
+                    for (int q = 0; q < NV; q++) bVh.st(q, ct, v[q]);
                 }
             }
             // ---- in-plane increments of this plane, kept for one plane ----
@@ -1728,8 +1771,9 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
             }
             if (o.parab) {
                 R Pi[NV];
-                parab_face<D>(Blk<R>(a.PF + (bx.woff / NV) * (NPF * dim) + D * NPF * bx.cells, bx.cells), c, o, pL, pR,
-                              rL, rR, Pi);
+                const Blk<R> bPf(a.PF + bx.poff + (long long)(D * NPF) * bx.pcells, bx.pcells);
+                const int pi = pidx<D>(bx, ci - bx.g[0], cj - bx.g[1], dim == 3 ? ck - bx.g[2] : 0);
+                parab_face<D>(bPf, pi, o, pL, pR, rL, rR, Pi);
 #pragma unroll
                 for (int q = 0; q < NV; q++) F[q] -= Pi[q];
             }
@@ -1797,7 +1841,9 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
                 }
                 double r = (double)lamt;
                 if (o.parab) {
-                    R rho_h = a.Vh[bx.woff + RHO * cs + cu];
+                    // the cell below the item along D, in the T_d layout
+                    const int su = (D == 0) ? 1 : (D == 1 ? bx.tp : (ci - bx.g[0] + 1 >= bx.tF ? 2 * bx.tHp : bx.tpl));
+                    const R rho_h = Blk<R>(a.Vh + bx.toff, bx.tcells).ld(RHO, ct - su);
                     r += (double)diff_coeff(o, rho_h, gam) * rdx2;
                 }
                 rate_loc = fmax(rate_loc, r);
