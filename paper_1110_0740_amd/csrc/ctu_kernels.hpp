@@ -66,16 +66,12 @@ struct KBox {
     long long toff;
     int tcells, tp, tpl, tF, tS, tHp;
     int tnt;  // rows are whole lines: the t^n kernel stores them nontemporally
-    // layout of the parabolic face slots (see pidx): NPF planes of pcells
-    // elements per direction from element poff of the field
-    long long poff;
-    int pcells, pp, pS, pHp;
-    int pnt;  // rows are whole lines (1), stored nontemporally (2)
 };
 
 // T_d fields, and V^{n+1/2} of parabolic runs, live on the region [g-1, g+n]
 // only (positions rx, ry, rz from its low corner) in an order of their own, in
-// which every row of a t^n tile is whole 128-byte lines that one block writes: row pitch tp and plane pitch tpl
+// which every row of a t^n tile is whole 128-byte lines that one block writes:
+// row pitch tp and plane pitch tpl
 // are padded to lines, the columns from tF on (strip tiles) are stored
 // transposed, ry fastest with pitch tHp, from tS; boxes on the flat t^n layout
 // keep its position order (tp = n[0] + 3).  The padding is written too.  Rows
@@ -90,19 +86,6 @@ __device__ __forceinline__ int tidx(const KBox &bx, int rx, int ry, int rz)
 {
     const int main = rz * bx.tpl + ry * bx.tp + rx, strip = bx.tS + (2 * rz + rx - bx.tF) * bx.tHp + ry;
     return rx < bx.tF ? main : strip;
-}
-
-// the same for the parabolic slots of the D-faces at positions fx, fy, fz from
-// the low corner of the box (0 .. n along D, 0 .. n-1 across): rows of the n
-// faces that k_pflux's tiles own, pitch pp in whole lines; the x faces at
-// fx = n[0] are a plane of their own from pS, fy fastest with pitch pHp.  At
-// 160^3 FP32 k_pflux took 186 us with the ghosted row pitch and 130 with this
-// layout, and the x sweep after it 265 and 214.  Every layout fits the ghosted
-// extent; where padded rows would not, rows keep the box's width.
-template <int D> __device__ __forceinline__ int pidx(const KBox &bx, int fx, int fy, int fz)
-{
-    const int main = (fz * (bx.n[1] + (D == 1)) + fy) * bx.pp + fx;
-    return (D == 0 && fx == bx.n[0]) ? bx.pS + fz * bx.pHp + fy : main;
 }
 
 // the step of a box: the plan's dt, halved per level of a multi-level plan
@@ -400,6 +383,46 @@ constexpr int PF_E = 5;   // viscous and resistive energy flux
 constexpr int PF_FN = 6;  // classical conduction flux: normal component
 constexpr int PF_FM = 7;  // ... and magnitude
 
+// Layout of a box's face slots: NPF planes of `cells` elements per direction
+// from element `off` of the field.  The D-faces at positions fx, fy, fz from
+// the low corner of the box (0 .. n along D, 0 .. n-1 across) are rows of the
+// n faces that k_pflux's tiles own, pitch pp in whole 128-byte lines; the x
+// faces at fx = n[0] are a plane of their own from pS, fy fastest with pitch
+// pHp.  At 160^3 FP32 k_pflux took 186 us with the ghosted row pitch and 130
+// with this layout, and the x sweep after it 265 and 214.  Where the padded
+// rows do not fit the box's share (NPF slots per direction and ghosted cell),
+// rows keep the box's width (pad = false).
+template <typename R> struct PLay {
+    long long off;
+    int cells, pp, pS, pHp;
+    bool pad;
+
+    __device__ __forceinline__ PLay(const KBox &bx, int dim)
+    {
+        constexpr long long line = 128 / (int)sizeof(R);
+        auto up = [](long long v) { return (v + line - 1) & ~(line - 1); };
+        const long long n0 = bx.n[0], n1 = bx.n[1], n2 = (dim == 3) ? bx.n[2] : 1;
+        const long long P = up(n0), H = up(n1), ns = NPF * dim;
+        const long long sx = P * n1 * n2 + H * n2, sy = P * (n1 + 1) * n2, sz = (dim == 3) ? P * n1 * (n2 + 1) : 0;
+        const long long size = up(max(sx, max(sy, sz))), share = bx.woff / NV * ns, first = up(share);
+        pad = first - share + ns * size <= ns * bx.cells;
+        off = pad ? first : share;
+        cells = (int)(pad ? size : bx.cells);
+        pp = (int)(pad ? P : n0);
+        pHp = (int)(pad ? H : n1);
+        pS = (int)(pp * n1 * n2);
+    }
+    template <int D> __device__ __forceinline__ int idx(const KBox &bx, int fx, int fy, int fz) const
+    {
+        const int main = (fz * (bx.n[1] + (D == 1)) + fy) * pp + fx;
+        return (D == 0 && fx == bx.n[0]) ? pS + fz * pHp + fy : main;
+    }
+    __device__ __forceinline__ Blk<R> slots(const R *PF, int D) const
+    {
+        return Blk<R>(PF + off + (long long)(D * NPF) * cells, cells);
+    }
+};
+
 template <int DIM> struct PTile {
     static constexpr int TX = (DIM == 3) ? 32 : NT;
     static constexpr int TY = (DIM == 3) ? 8 : 1;
@@ -417,6 +440,7 @@ template <typename R> struct PArgs {
     R *PF;               // face slots (workspace): NPF * DIM planes per cell
     KOpts o;
     int lm;              // planes per block along the marching axis
+    int nt;              // k_pflux stores padded rows nontemporally
 };
 
 // the energy slot plus the conduction flux of normal component Fn and
@@ -667,7 +691,8 @@ __global__ __launch_bounds__(NT) void k_pflux(PArgs<R> a)
     const KBox bx = a.boxes[tl.box];
     const KOpts &o = a.o;
     const R *Vb = a.V + bx.toff;
-    R *Pb = a.PF + bx.poff;
+    const PLay<R> pl(bx, DIM);
+    const int nt = pl.pad && a.nt;
     // load range [lo, hi] per axis (x, y, marching in 3D; x, marching in 2D)
     int lo[3] = { 0, 0, 0 }, hi[3] = { 0, 0, 0 };
 #pragma unroll
@@ -707,14 +732,14 @@ __global__ __launch_bounds__(NT) void k_pflux(PArgs<R> a)
         auto face = [&](auto Dc, bool real) {
             constexpr int D = decltype(Dc)::value;
             if (real) pflux_face<DIM, D>(P, dg, o, out);
-            const Blk<R> dst(Pb + (long long)(D * NPF) * bx.pcells, bx.pcells);
+            const Blk<R> dst = pl.slots(a.PF, D);
             const int fx = x - bx.g[0], fy = (DIM == 3 ? y : m) - bx.g[1], fz = (DIM == 3) ? m - bx.g[2] : 0;
-            if (fx < bx.pp && (real || bx.pnt)) {
+            if (fx < pl.pp && (real || pl.pad)) {
                 // (the x face past a row without padding goes to its own plane)
-                const int pi = (fz * (bx.n[1] + (D == 1)) + fy) * bx.pp + fx;
-                int pnt = bx.pnt;
-                asm volatile("" : "+v"(pnt));
-                if (__builtin_amdgcn_readfirstlane(pnt) == 2) {
+                const int pi = (fz * (bx.n[1] + (D == 1)) + fy) * pl.pp + fx;
+                int n = nt;
+                asm volatile("" : "+v"(n));
+                if (__builtin_amdgcn_readfirstlane(n)) {
 #pragma unroll
                     for (int q = 0; q < NPF; q++) dst.template st<2>(q, pi, out[q]);
                 } else {
@@ -723,7 +748,7 @@ __global__ __launch_bounds__(NT) void k_pflux(PArgs<R> a)
                 }
             }
             if (D == 0 && real && fx == bx.n[0]) {
-                const int pi = pidx<D>(bx, fx, fy, fz);
+                const int pi = pl.template idx<D>(bx, fx, fy, fz);
 #pragma unroll
                 for (int q = 0; q < NPF; q++) dst.st(q, pi, out[q]);
             }
@@ -1771,9 +1796,9 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
             }
             if (o.parab) {
                 R Pi[NV];
-                const Blk<R> bPf(a.PF + bx.poff + (long long)(D * NPF) * bx.pcells, bx.pcells);
-                const int pi = pidx<D>(bx, ci - bx.g[0], cj - bx.g[1], dim == 3 ? ck - bx.g[2] : 0);
-                parab_face<D>(bPf, pi, o, pL, pR, rL, rR, Pi);
+                const PLay<R> pl(bx, dim);
+                const int pi = pl.template idx<D>(bx, ci - bx.g[0], cj - bx.g[1], dim == 3 ? ck - bx.g[2] : 0);
+                parab_face<D>(pl.slots(a.PF, D), pi, o, pL, pR, rL, rR, Pi);
 #pragma unroll
                 for (int q = 0; q < NV; q++) F[q] -= Pi[q];
             }

@@ -425,7 +425,7 @@ void build_t_layout(ctu_plan *p)
 {
     const long long line = 128 / p->esize;
     auto up = [&](long long v) { return (v + line - 1) / line * line; };
-    long long off = 0, poff = 0;
+    long long off = 0;
     for (KBox &bx : p->hboxes) {
         const bool d3 = p->opts.dim == 3;
         const long long W = bx.n[0] + 2, H = bx.n[1] + 2, D = d3 ? bx.n[2] + 2 : 1;
@@ -462,28 +462,7 @@ void build_t_layout(ctu_plan *p)
         bx.toff = off;
         if (off % line != 0) bx.tnt = 0;
         off += NV * (long long)bx.tcells;
-        // the parabolic face slots: the largest direction's extent per slot
-        const long long n0 = bx.n[0], n1 = bx.n[1], n2 = d3 ? bx.n[2] : 1;
-        auto psize = [&](long long pp, long long pHp) {
-            const long long x = pp * n1 * n2 + pHp * n2, y = pp * (n1 + 1) * n2, z = d3 ? pp * n1 * (n2 + 1) : 0;
-            return std::max(x, std::max(y, z));
-        };
-        bx.pnt = up(psize(up(n0), up(n1))) <= bx.cells && poff % line == 0;
-        bx.pp = (int)(bx.pnt ? up(n0) : n0);
-        bx.pHp = (int)(bx.pnt ? up(n1) : n1);
-        bx.pS = (int)(bx.pp * n1 * n2);
-        bx.pcells = (int)(bx.pnt ? up(psize(bx.pp, bx.pHp)) : psize(bx.pp, bx.pHp));
-        bx.poff = poff;
-        poff += (long long)(NPF * p->opts.dim) * bx.pcells;
     }
-    // k_pflux stores past the caches where the slots of a plan would fill more
-    // than half of the 256 MiB last-level cache: 160^3 FP32 (393 MB) steps in
-    // 1371 us instead of 1388, 96 x 160^2 (236 MB) in 865 instead of 872, and
-    // 70 x 57 x 45 FP64 (34 MB), whose sweeps find the slots in the cache, in
-    // 212 instead of 208
-    if (poff * p->esize > 128ll << 20)
-        for (KBox &bx : p->hboxes)
-            if (bx.pnt) bx.pnt = 2;
 }
 
 // the tables that depend on the launch shape: t^n tiles and sweep columns,
@@ -716,6 +695,12 @@ template <typename R> hipError_t launch_pflux(ctu_plan *p, const R *V, int div, 
     pa.V = V;
     pa.PF = (R *)p->wsPF;
     pa.lm = div ? p->split_auto.lm_div : p->split_auto.lm_flux;
+    // k_pflux stores past the caches where the slots of a plan would fill more
+    // than half of the 256 MiB last-level cache: 160^3 FP32 (393 MB) steps in
+    // 1371 us instead of 1388, 96 x 160^2 (236 MB) in 865 instead of 872, and
+    // 70 x 57 x 45 FP64 (34 MB), whose sweeps find the slots in the cache, in
+    // 212 instead of 208
+    pa.nt = (int64_t)NPF * p->opts.dim * p->ws_cells * p->esize > (128ll << 20);
     pa.o = p->ko;
     if constexpr (sizeof(R) == 4) return launch_pflux_f32(p->opts.dim, div, (int)ts.n(), pa, s);
     else return launch_pflux_f64(p->opts.dim, div, (int)ts.n(), pa, s);
