@@ -98,19 +98,26 @@ __global__ __launch_bounds__(NT) void k_hcopy(const HBox *box, const HCopy *cp, 
     const HBox D = box[c.dst], S = box[c.src];
     const long long dp = D.off + ((long long)(c.dlo[2] + z) * D.N[1] + (c.dlo[1] + y)) * D.N[0] + (c.dlo[0] + x);
     const long long sp = S.off + ((long long)(c.slo[2] + z) * S.N[1] + (c.slo[1] + y)) * S.N[0] + (c.slo[0] + x);
+    // the copied cells are interior and the written ones ghosts: all loads
+    // first, where one store after the other would wait for its own load
+    R u[NV];
 #pragma unroll
-    for (int q = 0; q < NV; q++) U[dp + q * D.cells] = U[sp + q * S.cells];
+    for (int q = 0; q < NV; q++) u[q] = U[sp + q * S.cells];
+#pragma unroll
+    for (int q = 0; q < NV; q++) U[dp + q * D.cells] = u[q];
 }
 
 // Eq. prolong for the ghost cells no same-level box holds, one thread per
 // listed coarse parent: the parent's time-interpolated value (Eq. intalpha)
 // and the MC slopes of its six face neighbours give each masked child
 // u0 + sum_d (-+1/4) slope_d.  The nine variables are taken one after the
-// other (the loop is kept rolled), so that a wave has the 7-cell stencil of
-// one variable plane in flight rather than of all nine, which the L2 cannot
-// hold for the parents of a box's x-ghost slabs (two to a row).  (One thread
-// per parent and variable ran slower: each thread re-reads the parent's and
-// the box's records.)
+// other (the loop is kept rolled), the next one's 7-cell stencil loaded ahead
+// of the stores of this one, so that a wave has the stencils of two variable
+// planes in flight rather than of all nine, which the L2 cannot hold for the
+// parents of a box's x-ghost slabs (two to a row): 38 us per fill of the
+// base-64 three-level hierarchy instead of 43.  (One thread per parent and
+// one or three variables ran slower: each thread re-reads the parent's and the
+// box's records.)
 template <typename R>
 __global__ __launch_bounds__(NT) void k_hprolong(const HBox *box, const HPar *par, int npar, const int *multi,
                                                  const HBox *cbox, int N, int ng, R *U, const R *Uo, const R *Un,
@@ -133,25 +140,40 @@ __global__ __launch_bounds__(NT) void k_hprolong(const HBox *box, const HPar *pa
 #pragma unroll
         for (int t = 0; t < 7; t++) {
             int c[3] = { pi, pj, pk };
-            if (t > 0) c[(t - 1) / 2] = wrapi(c[(t - 1) / 2] + ((t & 1) ? -1 : 1), Nc);
+            if (t > 0) {
+                int &v = c[(t - 1) / 2];
+                v += (t & 1) ? -1 : 1;
+                v = v < 0 ? v + Nc : (v >= Nc ? v - Nc : v);
+            }
             const HBox C = cbox[m ? m[t] : P.cbox];
             base[t] = hidx(C, c[0], c[1], c[2], ng);
             cl[t] = C.cells;
         }
     }
     if (!ok && missing) atomicAdd(missing, __popc(P.mask));
-    auto val = [&](int t, int q) -> R {
-        const long long p = base[t] + (long long)q * cl[t];
-        return (alpha == R(0)) ? Uo[p] : (R(1) - alpha) * Uo[p] + alpha * Un[p];
+    R w[7];
+    auto load = [&](int q) {
+        if (!ok) return;
+#pragma unroll
+        for (int t = 0; t < 7; t++) w[t] = Uo[base[t] + (long long)q * cl[t]];
+        if (alpha != R(0)) {
+            R wn[7];
+#pragma unroll
+            for (int t = 0; t < 7; t++) wn[t] = Un[base[t] + (long long)q * cl[t]];
+#pragma unroll
+            for (int t = 0; t < 7; t++) w[t] = (R(1) - alpha) * w[t] + alpha * wn[t];
+        }
     };
+    load(0);
 #pragma unroll 1
     for (int q = 0; q < NV; q++) {
         R u0 = R(0), sl[3] = { R(0), R(0), R(0) };
         if (ok) {
-            u0 = val(0, q);
+            u0 = w[0];
 #pragma unroll
-            for (int d = 0; d < 3; d++) sl[d] = mc_slope(val(2 + 2 * d, q) - u0, u0 - val(1 + 2 * d, q));
+            for (int d = 0; d < 3; d++) sl[d] = mc_slope(w[2 + 2 * d] - u0, u0 - w[1 + 2 * d]);
         }
+        if (q + 1 < NV) load(q + 1);
         for (int c8 = 0; c8 < 8; c8++) {
             if (!(P.mask & (1u << c8))) continue;
             const long long li = ((long long)(P.f0[2] + ((c8 >> 2) & 1)) * b.N[1] + (P.f0[1] + ((c8 >> 1) & 1))) *

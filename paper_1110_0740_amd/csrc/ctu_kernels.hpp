@@ -1958,6 +1958,9 @@ __global__ __launch_bounds__(NT) void k_reflux(const KBox *boxes, const KRefl *e
     const KRefl first = ent[e0];
     const KBox &bx = boxes[first.box];
     const int c = cidx(bx, first.i, first.j, first.k);
+    R u[NV];
+#pragma unroll
+    for (int q = 0; q < NV; q++) u[q] = U[bx.uoff + q * bx.cells + c];
     double du[NV];
 #pragma unroll
     for (int q = 0; q < NV; q++) du[q] = 0.0;
@@ -1982,10 +1985,7 @@ __global__ __launch_bounds__(NT) void k_reflux(const KBox *boxes, const KRefl *e
         for (int q = 0; q < NV; q++) du[q] += en.scale * (fine[q] - rc[q]);
     }
 #pragma unroll
-    for (int q = 0; q < NV; q++) {
-        R *p = &U[bx.uoff + q * bx.cells + c];
-        *p = R((double)(*p) + du[q]);
-    }
+    for (int q = 0; q < NV; q++) U[bx.uoff + q * bx.cells + c] = R((double)u[q] + du[q]);
     if (consume) {
         for (int e = e0; e < e1; e++) {
             const KRefl en = ent[e];
