@@ -690,7 +690,7 @@ def leg_c3(args, dev, s, samples):
     # algorithmic bytes: ghosted reads, interior writes, register slots (read + write, FP64)
     alg_bytes = 36 * sum(ghost_l) + 36 * zones + 2 * 72 * nslots
     r_pl = result(ms_pl, zones, alg_bytes / zones, shape=shapes)
-    r_pl["launches_per_step"] = 6 * nlev + nlev - 1
+    r_pl["launches_per_step"] = 5 * nlev + nlev - 1
     del plans
     # one plan over every patch of every level, one graph per step
     log("C3: FP32 one plan over all levels")
@@ -727,7 +727,7 @@ def leg_c3(args, dev, s, samples):
     ms32 = timed(amr_step_one, K, W, s)
     assert b.fails.sum().item() == 0
     r32 = result(ms32, zones, alg_bytes / zones, one_kernels, shape1)
-    r32["launches_per_step"] = 7
+    r32["launches_per_step"] = 6
     r32["roofline"] = kernel_roofline("C2", one_kernels, zones, "f32")
     r32["levels"] = []
     for lev in range(nlev):
@@ -803,7 +803,7 @@ def c3_per_patch(h, U64, params, offs, okw, zones, ghost_l, npatch, b, s, K, W):
     ms64 = timed(amr_step64, K, W, s)
     assert b.fails.sum().item() == 0
     r64 = result(ms64, zones, 2 * (36 * sum(ghost_l) + 36 * zones) / zones)
-    r64["launches_per_step"] = 6 * npatch
+    r64["launches_per_step"] = 5 * npatch
     del pplans, Uo64
     return r64, ms64
 
