@@ -97,7 +97,18 @@ template <typename F> hipError_t with_phys(int phys, F &&f)
 
 }  // namespace
 
-struct ctu_plan {
+// The workspace fields of a plan (carve_ws sets them): V^n, the transverse
+// increments T_d, V^{n+1/2}, rate.  A step on another workspace saves and
+// restores them as one, so that no field can be left behind.
+struct WsPtrs {
+    void *wsV = nullptr, *wsT[3] = { nullptr, nullptr, nullptr };
+    void *wsVh = nullptr, *wsLam = nullptr;
+    void *wsPF = nullptr;  // parabolic face slots (NPF per face, dim faces per cell)
+    void *wsF[3] = { nullptr, nullptr, nullptr };  // MT corner coupling: predictor fluxes per direction
+    unsigned char *wsFlag = nullptr;  // App. B zone flags (one byte per cell) or null
+};
+
+struct ctu_plan : WsPtrs {
     int dev = 0;  // HIP device of the tables, the workspace and every launch
     ctu_opts opts;
     KOpts ko;
@@ -116,12 +127,6 @@ struct ctu_plan {
     TileSet t_cells, t_tc, t_sweep[3], t_cfl;
     TileSet t_mt[3];  // MT corner coupling: 4 x 64 face tiles per direction
     TileSet t_pf, t_pd;  // parabolic fluxes: k_pflux / k_pdiv tiles (in-plane tiles by marching chunks)
-    // workspace fields: V^n, the transverse increments T_d, V^{n+1/2}, rate
-    void *wsV = nullptr, *wsT[3] = { nullptr, nullptr, nullptr };
-    void *wsVh = nullptr, *wsLam = nullptr;
-    void *wsPF = nullptr;  // parabolic face slots (NPF per face, dim faces per cell)
-    void *wsF[3] = { nullptr, nullptr, nullptr };  // MT corner coupling: predictor fluxes per direction
-    unsigned char *wsFlag = nullptr;  // App. B zone flags (one byte per cell) or null
     int64_t ws_bytes = 0;      // bytes of the workspace block the option set needs
     void *ws_block = nullptr;  // library-allocated workspace block (null: caller-owned or not yet set)
     bool has_ws = false;       // a workspace is in place
@@ -1599,28 +1604,6 @@ ctu_status scratch_address(int dev, void **out)
     return CTU_OK;
 }
 
-// workspace pointers of a plan, saved around a step on the scratch
-struct WsPtrs {
-    void *V, *T[3], *Vh, *Lam, *F[3];
-    unsigned char *Flag;
-    explicit WsPtrs(const ctu_plan *p)
-        : V(p->wsV), T{ p->wsT[0], p->wsT[1], p->wsT[2] }, Vh(p->wsVh), Lam(p->wsLam),
-          F{ p->wsF[0], p->wsF[1], p->wsF[2] }, Flag(p->wsFlag)
-    {
-    }
-    void restore(ctu_plan *p) const
-    {
-        p->wsV = V;
-        p->wsVh = Vh;
-        p->wsLam = Lam;
-        p->wsFlag = Flag;
-        for (int d = 0; d < 3; d++) {
-            p->wsT[d] = T[d];
-            p->wsF[d] = F[d];
-        }
-    }
-};
-
 }  // namespace
 
 extern "C" {
@@ -1643,14 +1626,14 @@ ctu_status ctu_step_static(ctu_plan *plan, const void *U_in_dev, void *U_out_dev
     if ((st = scratch_address(plan->dev, &ptr)) != CTU_OK) return st;
     // every scratch field is written before it is read within the step, so
     // nothing needs clearing; the previous call's contents are overwritten
-    const WsPtrs saved(plan);
+    const WsPtrs saved = *plan;
     carve_ws(plan, (char *)ptr);
     hipStream_t s = (hipStream_t)stream;
     st = (plan->esize == 4) ? enqueue_step<float>(plan, U_in_dev, U_out_dev, params_dev, cool_L0_dev, reg_dev,
                                                   rate_dev, dpp_dev, fails_dev, s)
                             : enqueue_step<double>(plan, U_in_dev, U_out_dev, params_dev, cool_L0_dev, reg_dev,
                                                    rate_dev, dpp_dev, fails_dev, s);
-    saved.restore(plan);
+    static_cast<WsPtrs &>(*plan) = saved;
     return st;
 }
 
