@@ -530,7 +530,6 @@ __device__ __forceinline__ void hlld_state(const R *VL, const R *VR, R *F, R &sm
     const R aL = (SL - uL) * VL[RHO], aR = (SR - uR) * VR[RHO];
     const R iden = rcp(aR - aL);
     const R SM = (aR * uR - aL * uL - pt[1] + pt[0]) * iden;
-    const R pts = (aR * pt[0] - aL * pt[1] + aL * aR * (uR - uL)) * iden;
 
     // single-star values; index 0 = left, 1 = right
     R rs[2], vt[2], vb[2], Bt[2], Bb[2], iS[2], sr[2], isr[2];
@@ -579,17 +578,23 @@ __device__ __forceinline__ void hlld_state(const R *VL, const R *VR, R *F, R &sm
         if (q != BX1 + n) Vk[q] = k ? VR[q] : VL[q];
     const R uk = Vk[MX1 + n], ptk = k ? pt[1] : pt[0];
     const R Ek = Vk[PRS] * igm1 + R(0.5) * Vk[RHO] * (sq(Vk[MX1]) + sq(Vk[MX2]) + sq(Vk[MX3])) + (ptk - Vk[PRS]);
+    // the total pressure at the interface: the star's differs from side k's by
+    // dpt = a_k (S_M - u_k), a small correction, where the quotient that both
+    // sides share would round several times at p_t; the momentum flux adds dpt
+    // to rho u^2 first
+    const R Su = (k ? SR : SL) - uk;
+    const R dpt = outer ? R(0) : Su * Vk[RHO] * (SM - uk), pX = ptk + dpt;
     const R vBk = uk * Bn + Vk[MX1 + t] * Vk[BX1 + t] + Vk[MX1 + b] * Vk[BX1 + b];
     const R vtk = k ? vt[1] : vt[0], vbk = k ? vb[1] : vb[0];
     const R Btk = k ? Bt[1] : Bt[0], Bbk = k ? Bb[1] : Bb[0];
     const R vBs = SM * Bn + vtk * Btk + vbk * Bbk;
     const R vBss = SM * Bn + vtt * Btt + vbb * Bbb;
-    const R Es = (((k ? SR : SL) - uk) * Ek - ptk * uk + pts * SM + Bn * (vBk - vBs)) * (k ? iS[1] : iS[0]);
+    const R Es = (Su * Ek - ptk * uk + pX * SM + Bn * (vBk - vBs)) * (k ? iS[1] : iS[0]);
     const R Ess = Es + (k ? sr[1] : -sr[0]) * (vBs - vBss) * sB;
 
     // the state at the interface and its flux
     const R ro = outer ? Vk[RHO] : (k ? rs[1] : rs[0]);
-    const R u = outer ? uk : SM, pX = outer ? ptk : pts;
+    const R u = outer ? uk : SM;
     const R vtX = outer ? Vk[MX1 + t] : (single ? vtk : vtt), vbX = outer ? Vk[MX1 + b] : (single ? vbk : vbb);
     const R BtX = outer ? Vk[BX1 + t] : (single ? Btk : Btt), BbX = outer ? Vk[BX1 + b] : (single ? Bbk : Bbb);
     const R EX = outer ? Ek : (single ? Es : Ess);
@@ -597,7 +602,7 @@ __device__ __forceinline__ void hlld_state(const R *VL, const R *VR, R *F, R &sm
     const R du = (!outer & ((k & dg[1]) | (!k & dg[0]))) ? uk - SM : R(0);
     const R m = ro * u;
     F[RHO] = m;
-    F[MX1 + n] = m * u + (pX - Bn2);
+    F[MX1 + n] = (m * u + dpt) + (ptk - Bn2);
     F[MX1 + t] = m * vtX - Bn * BtX;
     F[MX1 + b] = m * vbX - Bn * BbX;
     F[ENG] = (EX + pX) * u - vBX * Bn;
