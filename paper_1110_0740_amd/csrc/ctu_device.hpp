@@ -1157,17 +1157,18 @@ template <typename R> __device__ __forceinline__ R minmod(R a, R b)
 // for differences of one sign, that sign times min(|dp + dm|/4, |dp|, |dm|).
 // FP32 nests the medians (minmod of three = minmod(x, minmod(y, z)), and
 // halving is exact): two v_med3_f32 in place of the sign test and selects.
-// FP64, which has no median, clamps the quarter sum to the interval from 0
-// to the difference of smaller magnitude: six minima and maxima in place of a
-// product, two comparisons and two-register selects.
+// FP64, which has no median, keeps the sign test, on the quarter sum: a NaN
+// difference gives a flat slope, where minima and maxima alone would pass the
+// other one on (192^3: 2643 us a step, 2637 with those, 2648 with the test on
+// the result).
 __device__ __forceinline__ float lim_mc_half(float dp, float dm)
 {
     return __builtin_amdgcn_fmed3f(0.25f * (dp + dm), __builtin_amdgcn_fmed3f(dp, dm, 0.0f), 0.0f);
 }
 __device__ __forceinline__ double lim_mc_half(double dp, double dm)
 {
-    const double lo = fmin(fmax(dp, dm), 0.0), hi = fmax(fmin(dp, dm), 0.0);
-    return fmax(fmin(0.25 * (dp + dm), hi), lo);
+    const double c = (dp * dm > 0.0) ? 0.25 * (dp + dm) : 0.0;
+    return copysign(fmin(fmin(fabs(c), fabs(dp)), fabs(dm)), c);
 }
 template <typename R> __device__ __forceinline__ R lim_mc(R dp, R dm) { return R(2) * lim_mc_half(dp, dm); }
 

@@ -67,6 +67,7 @@ void t_rcp(int n, const double *a, double *r) { for (int i = 0; i < n; i++) r[i]
 void t_quot(int n, const double *a, const double *b, double *r) { for (int i = 0; i < n; i++) r[i] = ctu::quot(a[i], b[i]); }
 void t_root(int n, const double *a, double *r) { for (int i = 0; i < n; i++) r[i] = ctu::root(a[i]); }
 void t_rsq(int n, const double *a, double *r) { for (int i = 0; i < n; i++) r[i] = ctu::rsq(a[i]); }
+void t_mc(int n, const double *a, const double *b, double *r) { for (int i = 0; i < n; i++) r[i] = ctu::lim_mc(a[i], b[i]); }
 // HLLD fluxes of n pairs of states (9 values each) along x: as the library
 // forms them in FP64, in the jump form, and the jump form in long double,
 // rounded to FP64 with its remainder
@@ -144,6 +145,24 @@ def test_operators_at_zero_infinity_and_nan(dev):
         assert np.array_equal(call(dev.t_quot, a, b), a / b, equal_nan=True)
     # the reciprocal root is for positive finite arguments: NaN elsewhere
     assert np.isnan(call(dev.t_rsq, np.append(s, -1.0))).all()
+
+
+def mc_selects(dp, dm):
+    """the monotonised central limiter by its sign test"""
+    c = 0.5 * (dp + dm)
+    m = np.fmin(np.fmin(np.abs(c), 2.0 * np.abs(dp)), 2.0 * np.abs(dm))
+    return np.where(dp * dm > 0.0, np.copysign(m, c), 0.0)
+
+
+def test_mc_limiter_is_flat_next_to_nan(dev):
+    rng = np.random.default_rng(3)
+    v = np.concatenate([SPECIAL, [1.0, -1.0, 3.0, -3.0, 1e-170, -1e-170, 5e-324], rng.standard_normal(200)])
+    dp, dm = (x.reshape(-1) for x in np.meshgrid(v, v))
+    with np.errstate(all="ignore"):
+        ref = mc_selects(dp, dm)
+    got = call(dev.t_mc, dp, dm)
+    assert np.array_equal(got, ref)
+    assert (got[np.isnan(dp) | np.isnan(dm)] == 0.0).all()
 
 
 def states(n, dv, seed):
