@@ -106,6 +106,7 @@ struct WsPtrs {
     void *wsPF = nullptr;  // parabolic face slots (NPF per face, dim faces per cell)
     void *wsF[3] = { nullptr, nullptr, nullptr };  // MT corner coupling: predictor fluxes per direction
     unsigned char *wsFlag = nullptr;  // App. B zone flags (one byte per cell) or null
+    int cset = 0;  // the failure counters that go with them (see dcnt)
 };
 
 struct ctu_plan : WsPtrs {
@@ -153,7 +154,12 @@ struct ctu_plan : WsPtrs {
     // graph
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
-    int *dcnt = nullptr;  // the primitive recovery's failure counters, zero between steps
+    // the primitive recovery's failure counters: eight of the plan's workspace
+    // and eight of the static scratch (whose step may run beside the plan's),
+    // each zero between steps; cleft: a step ended between the kernel that
+    // counts and the one that clears
+    int *dcnt = nullptr;
+    bool cleft[2] = { false, false };
     hipEvent_t tune_ev[2] = { nullptr, nullptr };  // autotuner timing events
     // per-stage event timing
     bool timing = false;
@@ -717,8 +723,15 @@ ctu_status enqueue_step(ctu_plan *p, const void *U_in, void *U_out, const double
 {
     const int dim = p->opts.dim;
     const bool par = p->opts.parabolic_mask != 0;
-    const FailCounts cnt{ fails ? p->dcnt : nullptr, (int *)fails, acc };
+    const FailCounts cnt{ fails ? p->dcnt + 8 * p->cset : nullptr, (int *)fails, acc };
     const R gam = (R)p->opts.gamma;
+    if (fails) {
+        if (p->cleft[p->cset]) {
+            hipLaunchKernelGGL(k_reset<0>, dim3(1), dim3(64), 0, s, (double *)nullptr, (double *)nullptr, cnt.plan);
+            HIP_TRY(hipGetLastError());
+        }
+        p->cleft[p->cset] = true;  // until the kernel that clears them is queued
+    }
     {
         StageTimer tm(p, 0, s);
         HIP_TRY(with_phys(p->combo.phys, [&](auto P) {
@@ -789,6 +802,7 @@ ctu_status enqueue_step(ctu_plan *p, const void *U_in, void *U_out, const double
             e = launch_tcouple_f64(dim, par ? 1 : 0, p->combo, p->t_tc.n(), ta, s);
         if (e != hipSuccess) return fail(CTU_ERR_HIP, std::string("t^n kernel launch: ") + hipGetErrorString(e));
     }
+    if (fails) p->cleft[p->cset] = false;
     if (par) {
         StageTimer tm(p, 3, s);
         HIP_TRY(launch_pflux(p, (const R *)p->wsVh, 0, s));
@@ -1106,7 +1120,7 @@ static ctu_status create_plan(int32_t dev, uint32_t flags, const ctu_opts *opts,
         free_plan(p);
         return st;
     }
-    if ((st = upload(std::vector<int>(8, 0), &p->dcnt)) != CTU_OK) {
+    if ((st = upload(std::vector<int>(16, 0), &p->dcnt)) != CTU_OK) {
         free_plan(p);
         return st;
     }
@@ -1628,6 +1642,7 @@ ctu_status ctu_step_static(ctu_plan *plan, const void *U_in_dev, void *U_out_dev
     // nothing needs clearing; the previous call's contents are overwritten
     const WsPtrs saved = *plan;
     carve_ws(plan, (char *)ptr);
+    plan->cset = 1;
     hipStream_t s = (hipStream_t)stream;
     st = (plan->esize == 4) ? enqueue_step<float>(plan, U_in_dev, U_out_dev, params_dev, cool_L0_dev, reg_dev,
                                                   rate_dev, dpp_dev, fails_dev, s)
