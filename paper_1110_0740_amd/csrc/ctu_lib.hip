@@ -1260,7 +1260,7 @@ ctu_status ctu_plan_autotune(ctu_plan *plan, const void *U_in_dev, void *U_out_d
         // coordinate descent: t^n layout and chunk, x-sweep pencils, y / z
         // sweep segments, launch order
         const int layouts[] = { CTU_TC_AUTO, CTU_TC_TILES, CTU_TC_FLAT };
-        const int chunks[] = { 4, 8, 16, 32 };
+        const int chunks[] = { 0, 4, 8, 16, 32 };
         for (int L : layouts) {
             if (L != CTU_TC_TILES && !any_flat) continue;
             for (int ch : chunks) {
@@ -1278,8 +1278,18 @@ ctu_status ctu_plan_autotune(ctu_plan *plan, const void *U_in_dev, void *U_out_d
             c.x_pencils = P;
             if ((r = consider(c)) != CTU_OK) return r;
         }
-        const int segs[] = { 0, 2, 3, 4 };
+        // whole lines only where they leave no compute unit without a block:
+        // on smaller plans the automatic runs are shorter for that reason
+        long long lines = 1 << 30;
+        for (int D = 1; D < plan->opts.dim; D++) {
+            long long n = 0;
+            for (const KBox &b : plan->hboxes)
+                n += ((long long)b.n[0] * (plan->opts.dim == 3 ? b.n[3 - D] : 1) + 63) / 64;
+            lines = std::min(lines, n);
+        }
+        const int segs[] = { 0, 1, 2, 3, 4 };
         for (int S : segs) {
+            if (S == 1 && lines < kCus) continue;
             ctu_shape c = best;
             c.yz_segments = S;
             if ((r = consider(c)) != CTU_OK) return r;
