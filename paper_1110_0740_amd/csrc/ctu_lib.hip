@@ -1264,6 +1264,7 @@ ctu_status ctu_plan_autotune(ctu_plan *plan, const void *U_in_dev, void *U_out_d
         for (int L : layouts) {
             if (L != CTU_TC_TILES && !any_flat) continue;
             for (int ch : chunks) {
+                if (ch == 0 && plan->split_auto.lm == 4) continue;  // the next one
                 ctu_shape c = best;
                 c.tc_layout = L;
                 c.tc_chunk = ch;
@@ -1287,9 +1288,18 @@ ctu_status ctu_plan_autotune(ctu_plan *plan, const void *U_in_dev, void *U_out_d
                 n += ((long long)b.n[0] * (plan->opts.dim == 3 ? b.n[3 - D] : 1) + 63) / 64;
             lines = std::min(lines, n);
         }
+        // and no count that the automatic runs have on every line
+        auto auto_runs = [&](int S) {
+            for (const KBox &b : plan->hboxes)
+                for (int D = 1; D < plan->opts.dim; D++) {
+                    const int run = run_rows(b.n[D], plan->split_auto.rows[D]);
+                    if ((b.n[D] + run - 1) / run != S) return false;
+                }
+            return true;
+        };
         const int segs[] = { 0, 1, 2, 3, 4 };
         for (int S : segs) {
-            if (S == 1 && lines < kCus) continue;
+            if ((S == 1 && lines < kCus) || (S > 0 && auto_runs(S))) continue;
             ctu_shape c = best;
             c.yz_segments = S;
             if ((r = consider(c)) != CTU_OK) return r;
