@@ -33,8 +33,9 @@ FLAGS = [
 # approximate reciprocal / root (a few ulp) instead of the correctly rounded
 # expansions, and FP32 subnormals flushed to zero, which lets both map to
 # single instructions without range scaling (the state variables stay many
-# orders of magnitude above 1e-38); FP64 keeps the correctly rounded forms
-# and subnormals.
+# orders of magnitude above 1e-38).  FP64 keeps subnormals; its divisions and
+# roots in the kernels are refined from the hardware's seeds (rcp, quot, root
+# and rsq in ctu_device.hpp), the remaining operators correctly rounded.
 _F32 = ["-fno-hip-fp32-correctly-rounded-divide-sqrt", "-fgpu-flush-denormals-to-zero"]
 UNIT_FLAGS = {"ctu_inst_f32.hip": _F32, "ctu_inst_mt_f32.hip": _F32}
 

@@ -44,13 +44,19 @@ template <typename R> __device__ __forceinline__ R sq(R x) { return x * x; }
 // Reciprocal, quotient, square root and reciprocal square root.  FP32 takes
 // the hardware's approximations (the FP32 unit runs with approximate divide /
 // sqrt and flushed subnormals).  FP64 refines the hardware's seeds (relative
-// error about 2^-23) by Newton steps in fused arithmetic to the rounding of
-// the result, without the range scaling and final correct rounding of the
-// language's operators: 6 / 9 / 11 / 6 instructions instead of 11 / 11 / 17 /
-// 28, every one in the dependent chains of the Riemann solver and the
-// eigensystem, which run at two waves per SIMD (the FP64 t^n kernel spent 38 %
-// of its instructions in the operators).  div_fixup restores the results for
-// zero, infinite and NaN operands.
+// error about 2^-23) in fused arithmetic to within an ulp of the result, without
+// the range scaling and final correct rounding of the language's operators: the
+// reciprocal by two Newton-Raphson steps, the quotient by one more correction
+// with its residual, the root by a coupled Newton (Goldschmidt) step and a
+// residual correction, the reciprocal root by the series 1 + e/2 + 3 e^2 / 8 of
+// (1 - e)^(-1/2).  6 / 9 / 11 / 6 instructions instead of 11 / 11 / 17 / 28, every
+// one in the dependent chains of the Riemann solver and the eigensystem, which
+// run at two waves per SIMD (the FP64 t^n kernel spent 38 % of its instructions
+// in the operators).  div_fixup restores the results of rcp and quot for zero,
+// infinite and NaN operands, and root returns zeros and infinity unchanged.
+// rsq is for positive finite arguments and gives NaN elsewhere: its callers take
+// a state with rho, p or a star density of 0 (or infinity) to NaN either way,
+// since they multiply the reciprocal root by its argument.
 __device__ __forceinline__ float rcp(float x) { return 1.0f / x; }
 __device__ __forceinline__ double rcp(double x)
 {
@@ -498,9 +504,11 @@ __device__ __forceinline__ void rusanov(const R *VL, const R *VR, R *F, R &smax,
 // star states, and needs neither the outer fluxes nor the conserved states of
 // both sides nor the selects between them: the FP64 t^n kernel, four solves
 // per cell and plane, went from 2490 to 2128 instructions (192^3: 800 -> 775
-// us).  It rounds differently (1e-16); FP32 keeps its form, 1952 instructions
-// against 1645, because its t^n kernel is bound by its stores at size and the
-// rates, and with them the time steps, of FP32 runs stay the same to the bit.
+// us), and its flux rounds less: per row 0.56 (density), 0.89 (normal momentum),
+// 0.83 (transverse), 0.67 (energy) and 0.77 (field) of the jump form's mean
+// error, a whole step 0.95 (2D) to 0.99 (non-ideal) of it.  FP32 keeps its form,
+// 1952 instructions against 1645, because its t^n kernel is bound by its stores
+// at size and the results and rates of ideal FP32 runs stay the same to the bit.
 //
 // In the degenerate case (S -> S_M with B_t -> 0) the star keeps the transverse
 // field, which breaks the jump condition of the induction rows; they take u_k
@@ -542,7 +550,7 @@ __device__ __forceinline__ void hlld_state(const R *VL, const R *VR, R *F, R &sm
         iS[s] = rcp(SSM);
         rs[s] = a * iS[s];
         const R den = aS - Bn2;
-        dg[s] = fabs(den) <= R(sizeof(R) == 8 ? 1e-12 : 1e-6) * (fabs(aS) + Bn2);
+        dg[s] = fabs(den) <= R(1e-12) * (fabs(aS) + Bn2);
         const R iden2 = rcp(den);
         const R fv = dg[s] ? R(0) : Bn * (SM - u) * iden2;
         const R fB = dg[s] ? R(1) : (a * (S - u) - Bn2) * iden2;

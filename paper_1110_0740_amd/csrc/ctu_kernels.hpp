@@ -187,19 +187,19 @@ __device__ __forceinline__ double block_max(double v, double *red)
     return r;
 }
 
-template <int Z = 0> __global__ void k_reset(double *rate, double *dpp, int *fails)
+template <int Z = 0> __global__ void k_reset(double *rate, int *fails)
 {
     int t = threadIdx.x;
     if (t == 0 && rate) rate[0] = 0.0;
-    if (t == 1 && dpp) dpp[0] = 0.0;
     if (t >= 2 && t < 2 + 5 && fails) fails[t - 2] = 0;
 }
 
 // The failure counters of a step.  The primitive recovery counts into the
-// plan's own counters, which are zero between steps; the t^n kernel's first
-// block moves them into the caller's (added to them if `acc`) and clears them,
-// so that no launch of its own zeroes the caller's counters.  Kernels do this
-// last: a store ahead of the table loads would make them vector loads.
+// plan's own counters, which are zero between steps (the host clears them where
+// a step ended early); the t^n kernel's first block moves them into the
+// caller's (added to them if `acc`) and clears them, so that no launch of its
+// own zeroes the caller's counters.  Kernels do this last: a store ahead of the
+// table loads would make them vector loads.
 struct FailCounts {
     int *plan, *out;
     int acc;
@@ -802,7 +802,6 @@ __global__ __launch_bounds__(NT) void k_pdiv(PArgs<R> a)
     const KTile tl = a.tiles[blockIdx.x];
     const KBox bx = a.boxes[tl.box];
     const KOpts &o = a.o;
-    const int cs = (int)bx.cells;
     const R *Vb = a.V + bx.woff;
     R *Pb = a.PF + (bx.woff / NV) * (NPF * DIM);
     int lo[3] = { 0, 0, 0 }, hi[3] = { 0, 0, 0 };
@@ -1113,7 +1112,6 @@ __global__ __launch_bounds__(NT, (tc_waves<PAR, RS, VAR, R>())) void k_tcouple(T
     const KOpts o = variant_opts<VAR>(a.o);
     const R gam = R(o.gamma), ch = R(a.params[1]);
     const R hdt = R(0.5 * box_dt(bx, a.params));
-    const int cs = (int)bx.cells;
     const R *Vb = a.V + bx.woff;
     const Blk<R> bPf(PAR ? a.PF + (bx.woff / NV) * (NPF * DIM) : a.V, bx.cells);
     const Blk<R> bV(Vb, bx.cells);
@@ -1610,7 +1608,6 @@ __global__ __launch_bounds__(NT, (sweep_waves<VAR, R>())) void k_sweep(
     const KBox bx = a.boxes[tl.box];
     const KOpts o = variant_opts<VAR>(a.o);
     const int dim = o.dim;
-    const int cs = (int)bx.cells;
     const int nD = bx.n[D];
     const int Lc = nD + 2;
     // transverse axes of D (t0 < t1 by direction index)

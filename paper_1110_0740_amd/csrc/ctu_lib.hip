@@ -251,14 +251,19 @@ bool use_flat(const ctu_plan *p, const KBox &bx)
 // Work split of the sweeps.  A block runs in rounds of 256 items; longer
 // blocks repeat less work at their ends, shorter ones put more blocks on the
 // chip and leave a shorter tail.  SplitCost estimates a launch's time, in
-// units of one round's cost on a compute unit that holds `res` blocks (the
-// register-bound residence): whole batches of 256 * res blocks cost res
-// units per round and kStart rounds to start; the blocks left over run fewer to a compute unit, where a
-// round takes kConc units (one block alone is bound by the latency of its
-// ~1500 dependent instructions) plus kPro rounds to start.  Against measured
-// sweeps (64^3 .. 256^3, 131 x 97 x 75, FP32 and FP64, 1 .. 8 runs per line)
-// the estimate is within 12 %: 256^3 FP32 715 / 664 / 657 / 662 / 690 us with
-// 1 / 2 / 3 / 4 / 8 runs, 192^3 FP64 880 / 726 / 686 / 683 / 719.
+// units of one round's cost on a compute unit that holds `res` blocks: whole
+// batches of 256 * res blocks cost res units per round and kStart rounds to
+// start; the blocks left over run fewer to a compute unit, where a round takes
+// kConc units (one block alone is bound by the latency of its ~1400 dependent
+// instructions) plus kPro rounds to start.  res is the residence that the
+// registers of the fixed-option variants allow, 3 (FP32) or 2 (FP64); variants
+// that hold fewer or more blocks are split by the same rule.
+// Against measured y and z sweeps (64^3 .. 256^3, 131 x 97 x 75, 1 .. 8 runs
+// per line) the estimate ranks the runs of one size within 7 % from 160^3 FP32
+// and 192^3 FP64 up and within 19 % below, and the choice is at most 5 % (FP32)
+// or 8 % (FP64 at 64^3 and 131 x 97 x 75) behind the fastest of them.  256^3 FP32
+// y: 683 / 637 / 628 / 632 / 642 us with 1 / 2 / 3 / 4 / 8 runs, 630 chosen; 192^3
+// FP64 779 / 650 / 612 / 603 / 631, 601 chosen.
 constexpr int kCus = 256;
 
 struct SplitCost {
@@ -325,8 +330,7 @@ SplitCost row_cost(const ctu_plan *p, int D, int rows)
     return c;
 }
 
-// in-plane tiles of the t^n region and of the parabolic kernels (whose
-// overlapping k_pdiv tiles set the larger count)
+// in-plane tiles of the t^n region
 long long tc_tiles_per_plane(const ctu_plan *p, const KBox &bx)
 {
     if (p->opts.dim == 2) return (bx.n[0] + 2 + TTile<2>::TX - 1) / TTile<2>::TX;
@@ -343,7 +347,8 @@ template <typename F> long long plane_blocks(const ctu_plan *p, int lm, F per_pl
 }
 
 // The split of the fields that a shape leaves at 0; near ties go to the
-// candidate listed first.
+// candidate listed first.  The y / z candidates are 1 .. 8 runs of the first
+// box's lines and runs that fill whole rounds; one length serves every box.
 ctu_plan::Split auto_split(const ctu_plan *p)
 {
     ctu_plan::Split s;
@@ -362,12 +367,13 @@ ctu_plan::Split auto_split(const ctu_plan *p)
         }
         return std::make_pair(best, bt);
     };
-    // t^n kernel: four planes per block (256^3 FP32 933 us against 1004 / 1063
-    // with 8 / 16 planes, 192^3 FP64 882 / 903 / 959) while that is twelve
-    // batches of blocks or more, then two (131 x 97 x 75 FP64, 2.5 batches:
-    // 152 -> 135 us; 160^3 non-ideal, 10 batches: 381 -> 357), and one where
-    // two leave the chip's second batch half empty (64^3: 34 / 28 / 27 us with
-    // 4 / 2 / 1)
+    // t^n kernel: four planes per block (192^3 FP64 676 us against 697 / 742
+    // with 8 / 16 planes and 682 with 2; 256^3 FP32 836 against 830 / 879 and
+    // 874) while that is twelve batches of blocks or more, then two (131 x 97 x
+    // 75 FP64, 2.5 batches: 113 us with 4, 103 with 2; 160^3 non-ideal FP32, 10
+    // batches: 339 and 337), and one where two leave the chip's second batch
+    // half empty (us with 4 / 2 / 1: 64^3 FP32 30.2 / 24.3 / 24.2, 48^3 26.7 /
+    // 18.8 / 15.2, 32^3 26.5 / 16.6 / 11.4, 128^2 FP64 17.0 / 11.6 / 9.1)
     auto tct = [&](const KBox &bx) { return tc_tiles_per_plane(p, bx); };
     s.lm = plane_blocks(p, 4, tct) >= 12 * slots ? 4 : (2 * plane_blocks(p, 2, tct) >= 3 * slots ? 2 : 1);
     for (int D = 1; D < dim; D++) {
@@ -382,6 +388,11 @@ ctu_plan::Split auto_split(const ctu_plan *p)
     const auto xr = pick([&](int v) { return row_cost(p, 0, v); }, { 1022, 510, 254, 190, 126, 62, 30 });
     s.xp = xp.first;
     if (xr.second < 0.95 * xp.second) s.xrows = xr.first;
+    // parabolic kernels: the chunks' blocks counted for both with k_pflux's
+    // tiles over n + 2 planes.  The exact counts (k_pdiv's overlapping tiles are
+    // up to a fifth more, k_pflux has n + 1 planes) move the lines to smaller
+    // boxes, where the longer chunk loses in FP64 (k_pdiv 68^3 43 -> 48 us, 118^3
+    // 128 -> 132) and gains nothing in FP32 (85^3 28.5 / 28.0, 128^3 69.7 / 70.8)
     if (p->opts.parabolic_mask) {
         auto pt = [&](const KBox &bx) {
             return (long long)((bx.n[0] + PTile<3>::TX) / PTile<3>::TX) * ((bx.n[1] + PTile<3>::TY) / PTile<3>::TY);
@@ -727,7 +738,7 @@ ctu_status enqueue_step(ctu_plan *p, const void *U_in, void *U_out, const double
     const R gam = (R)p->opts.gamma;
     if (fails) {
         if (p->cleft[p->cset]) {
-            hipLaunchKernelGGL(k_reset<0>, dim3(1), dim3(64), 0, s, (double *)nullptr, (double *)nullptr, cnt.plan);
+            hipLaunchKernelGGL(k_reset<0>, dim3(1), dim3(64), 0, s, (double *)nullptr, cnt.plan);
             HIP_TRY(hipGetLastError());
         }
         p->cleft[p->cset] = true;  // until the kernel that clears them is queued
@@ -1355,7 +1366,6 @@ ctu_status ctu_step(ctu_plan *plan, const void *U_in_dev, void *U_out_dev, const
                      0);
 }
 
-
 ctu_status ctu_step_graph_capture(ctu_plan *plan, const void *U_in_dev, void *U_out_dev, const double *params_dev,
                                   const void *cool_L0_dev, double *reg_dev, double *rate_dev, double *dpp_dev,
                                   int32_t *fails_dev, void *stream)
@@ -1438,7 +1448,7 @@ ctu_status ctu_cfl_rate(ctu_plan *plan, const void *U_dev, double *rate_dev, voi
     DevGuard guard(plan->dev);
     HIP_TRY(guard.err);
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_reset<0>, dim3(1), dim3(64), 0, s, rate_dev, (double *)nullptr, (int *)nullptr);
+    hipLaunchKernelGGL(k_reset<0>, dim3(1), dim3(64), 0, s, rate_dev, (int *)nullptr);
     HIP_TRY(hipGetLastError());
     int nb = plan->t_cfl.n();
     HIP_TRY(with_phys(plan->combo.phys, [&](auto P) {
@@ -1481,7 +1491,7 @@ ctu_status ctu_cons_to_prim(ctu_plan *plan, const void *U_dev, void *V_dev, int3
     HIP_TRY(guard.err);
     hipStream_t s = (hipStream_t)stream;
     if (fails_dev) {
-        hipLaunchKernelGGL(k_reset<0>, dim3(1), dim3(64), 0, s, (double *)nullptr, (double *)nullptr, (int *)fails_dev);
+        hipLaunchKernelGGL(k_reset<0>, dim3(1), dim3(64), 0, s, (double *)nullptr, (int *)fails_dev);
         HIP_TRY(hipGetLastError());
     }
     int nb = plan->t_cells.n();
